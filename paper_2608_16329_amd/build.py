@@ -18,8 +18,18 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmlip.so")
-SOURCES = ["api.cpp", "angular_tables.cpp", "neighbors.hip", "fused.hip", "unfused.hip", "md.hip", "scratch.hip"]
 ARCH = "gfx950"
+# The fused kernel's matrix sums are read by vector instructions right away:
+# kept in vector registers they need no copies (the compiler's default for a
+# kernel of 512 registers is the accumulation file).
+VGPR_SUMS = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+# (source, object, further flags); the fused kernel's instantiations are built
+# in three parts
+SOURCES = [("api.cpp", "api", []), ("angular_tables.cpp", "angular_tables", []), ("neighbors.hip", "neighbors", []),
+           ("fused.hip", "fused_f64", ["-DMLIP_FUSED_PART=1"] + VGPR_SUMS),
+           ("fused.hip", "fused_f64_high", ["-DMLIP_FUSED_PART=2"] + VGPR_SUMS),
+           ("fused.hip", "fused_f32", ["-DMLIP_FUSED_PART=3"]),
+           ("unfused.hip", "unfused", []), ("md.hip", "md", []), ("scratch.hip", "scratch", [])]
 
 
 def hipcc() -> str:
@@ -35,9 +45,10 @@ def common_flags():
             "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc()] + common_flags() + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(entry) -> str:
+    src, name, flags = entry
+    obj = os.path.join(BUILD, name + ".o")
+    cmd = [hipcc()] + common_flags() + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{res.stdout}\n{res.stderr}")

@@ -137,6 +137,47 @@ void pack_fragments(const double* M, int nout, int nin, int precision, int vw, s
           }
 }
 
+// A row-major [nout][128] float64 matrix as digits for the 16x16x64 8-bit
+// integer MFMA, followed by one scale per row.  The integers of a row are
+// round(w s) = sum_i d_i 256^(6 - i) with digits in [-128, 127], where s takes
+// the row's largest weight to 0.99 x 2^55 (seven balanced digits hold 0.996 x
+// 2^55), and its scale is 2^56 / s (NaN for a row with an infinity or NaN,
+// whose digits are zero).  Digit i of the half hf (columns 64 hf ..) of output
+// tile t is fragment 14 t + 7 hf + i, 16 bytes at lane 16 g + c: byte 4 T + q
+// is row 16 t + c, column 64 hf + 16 T + 4 g + q.
+void pack_digits(const double* M, int nout, std::vector<double>* out) {
+  constexpr int W = kEncWidth, D = kWeightDigits;
+  const size_t at = out->size(), frag_doubles = size_t(nout) * W / 8 * D;
+  out->resize(at + frag_doubles + size_t(nout));
+  unsigned char* frag = reinterpret_cast<unsigned char*>(out->data() + at);
+  for (int o = 0; o < nout; ++o) {
+    double top = 0.0;
+    bool finite = true;
+    for (int c = 0; c < W; ++c) {
+      finite = finite && std::isfinite(M[size_t(o) * W + c]);
+      top = std::max(top, std::fabs(M[size_t(o) * W + c]));
+    }
+    // the weights by an exact power of two into (-1, 1), then the scale
+    int E = 0;
+    const double lead = finite && top > 0.0 ? std::frexp(top, &E) : 1.0;
+    const double down1 = std::ldexp(1.0, -E / 2), down2 = std::ldexp(1.0, -(E - E / 2));
+    const double s = 0.99 * 0x1p55 / lead;
+    (*out)[at + frag_doubles + size_t(o)] = finite ? std::ldexp(0x1p56 / s, E) : std::nan("");
+    for (int hf = 0; hf < 2; ++hf)
+      for (int g = 0; g < 4; ++g) {
+        unsigned char lane[D][16];
+        for (int b = 0; b < 16; ++b) {
+          const double v = finite ? M[size_t(o) * W + 64 * hf + 16 * (b / 4) + 4 * g + b % 4] * down1 * down2 * s : 0.0;
+          // an offset of 128 in every digit turns them into plain bytes
+          const uint64_t x = (uint64_t(int64_t(v + (v < 0 ? -0.5 : 0.5))) + 0x80808080808080ull) ^ 0x80808080808080ull;
+          for (int i = 0; i < D; ++i) lane[i][b] = (unsigned char)(x >> (8 * (D - 1 - i)));
+        }
+        unsigned char* p = frag + (size_t(o / 16) * 2 * D + size_t(hf) * D) * 1024 + (16 * g + o % 16) * 16;
+        for (int i = 0; i < D; ++i) std::memcpy(p + size_t(i) * 1024, lane[i], 16);
+      }
+  }
+}
+
 // Copy host values to the device in the kernel's arithmetic type.
 hipError_t upload(void* dev, const double* host, size_t n, size_t elem_bytes) {
   if (elem_bytes == sizeof(double)) return hipMemcpy(dev, host, n * sizeof(double), hipMemcpyHostToDevice);
@@ -416,7 +457,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   const int nin = (hp->lmax + 1) * k;
   ctx->n_enc = int(enc_tables(hp));
   ctx->n_head = int(head_tables(hp));
-  ctx->enc_stride = enc_table_elems(k, hp->enc_hidden);
+  ctx->enc_stride = enc_table_elems(k, hp->enc_hidden, hp->precision);
   ctx->head_stride = head_table_elems(nin, hp->reg_hidden);
   ctx->elem_bytes = hp->precision == 64 ? sizeof(double) : sizeof(float);
   const int prec = hp->precision;
@@ -425,7 +466,8 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   const int vw_hid = int(16 / ctx->elem_bytes);
   const int vw_out = std::min(vw_hid, k / 16);
 
-  // encoder tables -> [w0 b0 | (fragments(W_t) b_t)... | fragments(W_out) b_out]
+  // encoder tables -> [w0 b0 | (fragments(W_t) b_t)... | fragments(W_out) b_out],
+  // in float64 digits and row scales in place of each matrix's fragments
   std::vector<double> enc;
   enc.reserve(ctx->enc_stride * ctx->n_enc);
   const double* src = weights_host;
@@ -435,11 +477,13 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     enc.insert(enc.end(), p, p + 2 * W);
     p += 2 * W;
     for (int h = 1; h < hp->enc_hidden; ++h) {
-      pack_fragments(p, kEncWidth, kEncWidth, prec, vw_hid, &enc);
+      if (prec == 64) pack_digits(p, kEncWidth, &enc);
+      else pack_fragments(p, kEncWidth, kEncWidth, prec, vw_hid, &enc);
       enc.insert(enc.end(), p + W * W, p + W * W + W);
       p += W * W + W;
     }
-    pack_fragments(p, k, kEncWidth, prec, vw_out, &enc);
+    if (prec == 64) pack_digits(p, k, &enc);
+    else pack_fragments(p, k, kEncWidth, prec, vw_out, &enc);
     enc.insert(enc.end(), p + size_t(k) * W, p + size_t(k) * W + k);
   }
   // head tables -> [frag(A0) | frag(A0^T) | c0 | (frag(A_t) frag(A_t^T) c_t)... | a_out c_out]

@@ -10,9 +10,10 @@
 //      is cut into 16-pair chunks; all pairs of a chunk share one encoder
 //      table (pair conditioning, Section 3.2).
 //   B. Pass 1, one chunk per wavefront at a time: the radial encoder (Eq. 2)
-//      and its derivative in r run as MFMA 16x16x4 products with the
-//      16 pairs as one matrix dimension, the activation and its tangent
-//      stacked as two column tiles sharing every weight fragment.  The
+//      and its derivative in r run as MFMA products with the 16 pairs as one
+//      matrix dimension, the activation and its tangent as two column tiles
+//      sharing every weight fragment (float64: error-free on 8-bit integer
+//      digits, below; float32: 16x16x4).  The
 //      moment P_i = sum_j g_ang (x) g_rad (Eq. 4) is another MFMA product
 //      (K = pairs), accumulated into LDS.  The pre-cutoff output m and its
 //      tangent dm (2k values per pair) go to a fixed-size per-work-group
@@ -42,6 +43,10 @@
 // later product as B (contracting over its rows; k-step q covers rows
 // drow(q, 0..3)) or as A (X^T, same contraction); the host packs weight
 // fragments with the same row map.
+//
+// The file is compiled in three parts (MLIP_FUSED_PART), whose instantiations
+// build in parallel: 1 float64 to l_max 3 and the entry, 2 float64 with l_max
+// 4..5, 3 float32.
 #include "kernel_math.h"
 #include "mlip_internal.h"
 
@@ -77,49 +82,54 @@ template <typename R>
 __device__ __forceinline__ int drow(int q, int g) {
   return sizeof(R) == 8 ? 4 * q + g : 4 * g + q;
 }
-template <typename R>
-__device__ __forceinline__ int qof(int c) {
-  return sizeof(R) == 8 ? c >> 2 : c & 3;
-}
-template <typename R>
-__device__ __forceinline__ int gof(int c) {
-  return sizeof(R) == 8 ? c & 3 : c >> 2;
-}
-
-// Logistic sigmoid 1 / (1 + exp(-z)) in float64, written out so the VALU
-// cost stays low next to the MFMA work (on gfx950 float64 VALU instructions
-// and float64 MFMA share one pipe, so every instruction here delays the
-// matrix products):
+// Logistic sigmoid 1 / (1 + exp(-z)) in float64, written out so that the
+// vector instructions are few (they, not the matrix products, bound the
+// encoder):
 //  * exp(t), t = -z clamped to [-700, 700] (beyond that the sigmoid is 0 or 1
 //    to far below float64 resolution of the SiLU value), by Cody-Waite
 //    reduction t = n ln2 + r with |r| <= ln2/2, a degree-10 polynomial (the
-//    interpolant at Chebyshev nodes, below 3.4e-16 relative error) and a 2^n
-//    scaling;
+//    interpolant at Chebyshev nodes, below 3.4e-16 relative error) and n
+//    added to the exponent; n is rounded by adding 1.5 x 2^52, which leaves
+//    it in the low word as an integer;
 //  * 1 / (1 + e) from the hardware reciprocal estimate (relative error
-//    measured below 2^-24) refined by one Newton-Raphson step, which squares
-//    that error.
-__device__ __forceinline__ double sigmoid(double z) {
-  constexpr double kLog2e = 1.4426950408889634;
-  constexpr double kLn2Hi = 6.93147180369123816490e-01;  // ln2 split, high part exact in 32 bits
-  constexpr double kLn2Lo = 1.90821492927058770002e-10;
-  const double t = fmin(fmax(-z, -700.0), 700.0);
-  const double n = rint(t * kLog2e);
-  double r = fma(-n, kLn2Hi, t);
-  r = fma(-n, kLn2Lo, r);
-  // polynomial interpolating exp at the 11 Chebyshev nodes of [-ln2/2,
-  // ln2/2] (solved in 80-bit arithmetic, rounded to float64), highest power
-  // first; relative error below 3.4e-16 on the interval
-  constexpr double c[11] = {
-    2.762635356445665e-07,  2.764018186396873e-06, 2.4801504368699663e-05, 0.00019841170267682938,
-    0.0013888888932453442,  0.008333333385670185,  0.04166666666657336,    0.16666666666554397,
-    0.5000000000000006,     1.0000000000000067,    1.0};
-  double p = c[0];
+//    measured below 2^-24) refined by one third-order step, y (1 + e + e^2).
+// The constants are held in scalar registers (as vector constants the
+// compiler copies them for every fused multiply-add).
+struct SigmoidConst {
+  double log2e, ln2hi, ln2lo, shift, top, bottom, c[10];
+  __device__ __forceinline__ SigmoidConst()
+      : log2e(1.4426950408889634),
+        ln2hi(-6.93147180369123816490e-01),  // -ln2 split, high part exact in 32 bits
+        ln2lo(-1.90821492927058770002e-10),
+        shift(6755399441055744.0), top(700.0), bottom(-700.0),
+        // polynomial interpolating exp at the 11 Chebyshev nodes of [-ln2/2,
+        // ln2/2] (solved in 80-bit arithmetic, rounded to float64), highest
+        // power first, constant term 1
+        c{2.762635356445665e-07, 2.764018186396873e-06, 2.4801504368699663e-05, 0.00019841170267682938,
+          0.0013888888932453442, 0.008333333385670185, 0.04166666666657336, 0.16666666666554397,
+          0.5000000000000006, 1.0000000000000067} {
 #pragma unroll
-  for (int k = 1; k < 11; ++k) p = fma(p, r, c[k]);
-  const double d = 1.0 + ldexp(p, int(n));
+    for (int i = 0; i < 10; ++i) asm("" : "+s"(c[i]));
+    asm("" : "+s"(log2e), "+s"(ln2hi), "+s"(ln2lo), "+s"(shift), "+s"(top), "+s"(bottom));
+  }
+};
+__device__ __forceinline__ double sigmoid(double z, const SigmoidConst& k) {
+  const double t = fmin(fmax(-z, k.bottom), k.top);
+  const double y0 = fma(t, k.log2e, k.shift);
+  const double n = y0 - k.shift;
+  double r = fma(n, k.ln2hi, t);
+  r = fma(n, k.ln2lo, r);
+  double p = k.c[0];
+#pragma unroll
+  for (int i = 1; i < 10; ++i) p = fma(p, r, k.c[i]);
+  p = fma(p, r, 1.0);
+  const double e2 = __hiloint2double(__double2hiint(p) + (__double2loint(y0) << 20), __double2loint(p));
+  const double d = 1.0 + e2;
   const double y = __builtin_amdgcn_rcp(d);
-  return fma(fma(-d, y, 1.0), y, y);
+  const double e = fma(-d, y, 1.0);
+  return fma(fma(e, e, e), y, y);
 }
+__device__ __forceinline__ double sigmoid(double z) { return sigmoid(z, SigmoidConst()); }
 
 // Logistic sigmoid in float32 from the hardware base-2 exponential and
 // reciprocal (each within about one ulp).  For large -z the exponential
@@ -265,7 +275,10 @@ struct Smem {
   // Pass 1 reads the first-layer weights; the head runs after pass 1 and
   // before the next tile is staged, so its activations reuse those bytes.
   union {
-    R l0[kMaxSpecies][2][kEncWidth];  // w0, b0 of the tile's encoder tables, by neighbour species
+    struct {
+      R l0[kMaxSpecies][2][kEncWidth];  // w0, b0 of the tile's encoder tables, by neighbour species
+      R geo[NW][16][4];                 // unit vector and cutoff function of each wavefront's 16 pairs
+    } p1;
     struct {
       R xT[(NM == 20 ? 4 : 6) * K][TM > 16 ? 32 : 16];  // head input vec(G), feature-major
       R yT[kHeadWidth][TM > 16 ? 32 : 16];             // head activations
@@ -304,6 +317,16 @@ struct Smem {
   int na;
 };
 
+// Thread index, renewed for a phase of the kernel: what is computed from it
+// (lane numbers, LDS and fragment offsets) is formed again in that phase.
+// Left to itself the compiler forms all of it once before the tile loop, and
+// the registers that hold it are then missing in the encoder.
+__device__ __forceinline__ int phase_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Position of the neighbour in column c of chunk ch (or a dummy), fetched
 // one chunk ahead so its latency overlaps the previous chunk's work.
 struct PairPos {
@@ -336,7 +359,7 @@ __device__ __forceinline__ int grab_chunk(int* counter) {
 
 template <int K, int TM, typename R, int NW, int DR, int NM>
 __device__ __forceinline__ PairPos load_pair_pos(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int ch) {
-  const int c = threadIdx.x & 15;
+  const int c = phase_tid() & 15;
   PairPos p{0.0, 0.0, 0.0};
   if (c < S.ch_count[ch]) {
     const long long j = S.pair_j[S.ch_start[ch] + c];
@@ -367,7 +390,7 @@ struct FragStream {
   int lo;
   __device__ __forceinline__ FragStream(const void* base, int bytes)
       : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRawBufferConfig)),
-        lo(int(threadIdx.x & 63) * int(sizeof(V))) {}
+        lo((phase_tid() & 63) * int(sizeof(V))) {}
   __device__ __forceinline__ V operator[](int e) const {
     const int so = e * 64 * int(sizeof(V));
     if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rs, lo, so, 0));
@@ -395,6 +418,17 @@ struct BiasStream {
   }
 };
 
+// Per-row values (float64) of a weight matrix at a wave-uniform address: the
+// four rows 16 To + 4 g + q of a lane.
+struct RowStream {
+  const double* p;
+  __device__ __forceinline__ RowStream(const double* base, int g) : p(base + 4 * g) {}
+  __device__ __forceinline__ void load(int To, double (&v)[4]) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = p[16 * To + q];
+  }
+};
+
 template <int K, typename R>
 struct Stream {
   static constexpr int KT = K / 16;
@@ -408,12 +442,148 @@ struct Stream {
   typedef R vo_t __attribute__((ext_vector_type(VO)));
 };
 
+// Row of the encoder's hidden activations held in register q of a lane of
+// group g, within a 16-row tile (both types), and the order in which pass 2
+// contracts the columns of m.
+__device__ __forceinline__ int hrow(int q, int g) { return 4 * g + q; }
+
+// ---- float64 products on the 8-bit integer matrix pipe ----------------------
+// A float64 MFMA runs at the rate of float64 FMAs and holds the vector pipe
+// for its whole duration; 8-bit integer MFMAs run 64 times as fast and leave
+// the vector pipe free.  The encoder's float64 products are therefore split
+// error-free (Ozaki's scheme): with a scale per weight row and per activation
+// column, both operands become 56-bit integers written as seven balanced
+// base-256 digits, X = sum_i d_i 256^(6-i), d_i in [-128, 127], and
+//   sum_k X_k Y_k = sum_i sum_j 256^(12-i-j) sum_k d_i[k] e_j[k],
+// whose inner sums are exact in 32 bits (128 products of at most 2^14, at
+// most seven of them per i + j: below 2^24).  The 28 digit products with
+// i + j <= 6 are formed; what is left out is below 2^-53 of the result's size
+// (measured against a float64 reference the outputs are as close as with
+// float64 MFMAs: 7.7e-16, 4.6e-15 and 4.0e-15 of E, F and w at 1,048,576 atoms,
+// 8.1e-16, 4.6e-15 and 4.0e-15 before).  An encoder call of 16 pairs (two
+// hidden layers) takes 59 thousand cycles at 2.1 GHz, 28 us, instead of 91
+// thousand at 2.34 GHz, 39 us; the kernel 198.6 ms instead of 251.0 ms at
+// 1,048,576 atoms of six species.  What bounds it now is vector issue: about
+// 76 vector instructions per activation and tangent beside 28 MFMAs.
+constexpr int kDigits = 7;
+typedef int v4i __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+}
+
+// Activation columns in digits: s[i][hf] holds digit i of the rows
+// 64 hf + 16 t + 4 g + q of column c in byte 4 t + q, which is both the B
+// operand (rows as k) and the A operand (columns as rows) of a 16x16x64
+// product.  inv: value of one unit of 2^32 of the integers.
+struct Digits {
+  v4i s[kDigits][2];
+  double inv;
+};
+
+// Scale that takes a column's largest magnitude (over the lane's 32 values
+// and its column's four lanes) to just below 0.99 x 2^23: the closer to the
+// full range, the less the digit products that are left out weigh.  A column
+// with an infinity or NaN gets a NaN inverse, so everything formed from it is
+// NaN; one of zeros (or below 2^-974) gets scale and inverse zero.
+__device__ __forceinline__ double digit_scale(const double (&h)[8][4], Digits& d) {
+  // largest magnitude by the high words: as signed integers for positive
+  // values, as unsigned for negative ones
+  int mp = 0;
+  unsigned mn = 0;
+#pragma unroll
+  for (int T = 0; T < 8; ++T)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int hi = __double2hiint(h[T][q]);
+      mp = max(mp, hi);
+      mn = max(mn, unsigned(hi));
+    }
+  unsigned m = max(unsigned(mp), mn >> 31 ? mn & 0x7fffffffu : 0u);
+  m = max(m, unsigned(__shfl_xor(int(m), 16, 64)));
+  m = max(m, unsigned(__shfl_xor(int(m), 32, 64)));
+  const double top = __hiloint2double(int(m + 1), 0);  // above every magnitude of the column
+  constexpr double kRange = 0.99 * 8388608.0;          // seven balanced digits hold 0.996 x 2^23 x 2^32
+  const double y = __builtin_amdgcn_rcp(top);
+  double scale = kRange * fma(fma(-top, y, 1.0), y, y);
+  double inv = top * (1.0 / kRange);
+  inv = fma(fma(-scale, inv, 1.0), inv, inv);
+  if (m - 0x03100000u >= 0x7fd00000u - 0x03100000u) {
+    scale = 0.0;
+    inv = m >= 0x7fd00000u ? __hiloint2double(0x7ff80000, 0) : 0.0;
+  }
+  d.inv = inv;
+  return scale;
+}
+
+// Digits of the half hf of a lane's values (tiles 4 hf .. 4 hf + 3): the value
+// is rounded to an integer and a remainder, the remainder to 32 bits, by
+// adding 1.5 x 2^52, which leaves the integers in the low words (and the
+// remainder's carry in its high word).  An offset of 128 in every digit
+// (0x808080 in the upper 24 bits, 0x80808080 in the lower 32) makes the digits
+// the bytes of a non-negative integer, up to the offset itself, taken off by
+// flipping each byte's top bit.
+__device__ __forceinline__ void make_digits(const double (&h)[8][4], double scale, int hf, Digits& d) {
+  constexpr double kShift = 6755399441055744.0;
+  double upper = kShift + 8421504.0, lower = kShift + 2155905152.0, two32 = 4294967296.0;
+  // opaque, or their copies for accumulating instructions would outnumber
+  // the arithmetic
+  asm("" : "+s"(upper), "+s"(two32));
+  asm("" : "+v"(lower));
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    unsigned hw[4], lw[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double x = h[4 * hf + t][q];
+      const double y = fma(x, scale, upper);
+      const double rem = fma(x, scale, upper - y);
+      const double v = fma(rem, two32, lower);
+      lw[q] = unsigned(__double2loint(v));
+      hw[q] = unsigned(__double2loint(y)) + unsigned(__double2hiint(v)) - 0x43380000u;
+    }
+    // 4 x 4 byte transposes
+    const unsigned a = __builtin_amdgcn_perm(hw[1], hw[0], 0x05010400u), b = __builtin_amdgcn_perm(hw[3], hw[2], 0x05010400u);
+    const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
+    const unsigned p = __builtin_amdgcn_perm(lw[1], lw[0], 0x07030602u), q = __builtin_amdgcn_perm(lw[3], lw[2], 0x07030602u);
+    const unsigned r = __builtin_amdgcn_perm(lw[1], lw[0], 0x05010400u), z = __builtin_amdgcn_perm(lw[3], lw[2], 0x05010400u);
+    const unsigned w[kDigits] = {
+        __builtin_amdgcn_perm(f, e, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u),
+        __builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(q, p, 0x07060302u),
+        __builtin_amdgcn_perm(q, p, 0x05040100u), __builtin_amdgcn_perm(z, r, 0x07060302u),
+        __builtin_amdgcn_perm(z, r, 0x05040100u)};
+#pragma unroll
+    for (int i = 0; i < kDigits; ++i) d.s[i][hf][t] = int(w[i] ^ 0x80808080u);
+  }
+  // kept in accumulation registers: matrix operands only from here on
+#pragma unroll
+  for (int i = 0; i < kDigits; ++i) asm("" : "+a"(d.s[i][hf]));
+}
+__device__ __forceinline__ void make_digits(const double (&h)[8][4], Digits& d) {
+  const double scale = digit_scale(h, d);
+  make_digits(h, scale, 0, d);
+  make_digits(h, scale, 1, d);
+}
+
+// Sum of the digit products, S[d] = sum over i + j = d, in units of 2^88:
+// 2^8 sum_d S[d] 2^(-8d), exact up to the last rounding (and to 2^-40 of a
+// unit of S[0]).  The pairs that are merged as integers stay below 2^31.
+__device__ __forceinline__ double digit_sum(const v4i (&S)[kDigits], int q) {
+  const int a = (S[0][q] << 8) + S[1][q], b = (S[2][q] << 8) + S[3][q], e = S[5][q] + (S[6][q] >> 8);
+  double t = fma(double(S[4][q]), 0x1p-8, double(b));
+  t = fma(double(e), 0x1p-16, t);
+  return fma(t, 0x1p-16, double(a));
+}
+
+// Weight tile of an integer product: digit i of half hf is fragment 7 hf + i
+// (64 lanes of 16 bytes).
+constexpr int kTileFrags = 2 * kDigits;
+
 // Minimum-image vector r_ij of the pair in column c of chunk ch (Eq. 1), in
 // float64; (1, 0, 0) and atom -1 for the padding columns of a partial chunk.
 template <int K, int TM, typename R, int NW, int DR, int NM>
 __device__ __forceinline__ void pair_delta(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int ch,
                                            const PairPos& pp, double* dx, double* dy, double* dz, int* atom) {
-  const int c = threadIdx.x & 15;
+  const int c = phase_tid() & 15;
   *dx = 1.0; *dy = 0.0; *dz = 0.0; *atom = -1;
   if (c >= S.ch_count[ch]) return;
   const int a = S.pair_a[S.ch_start[ch] + c];
@@ -434,22 +604,39 @@ __device__ __forceinline__ const R* chunk_table(const FusedArgs& A, const Smem<K
   return static_cast<const R*>(A.enc) + (long long)tau * A.enc_stride;
 }
 
+// What the hidden layers leave for the output layer: float32 the activations
+// and their tangents (rows 16T + 4g + i of column c), float64 their digits.
+template <typename R>
+struct Hidden;
+template <>
+struct Hidden<float> {
+  float h[8][4], dh[8][4];
+};
+template <>
+struct Hidden<double> {
+  Digits h, dh;
+};
+
 // Encoder forward and tangent (Eq. 2 and its derivative in r) up to the last
 // hidden layer for the 16 pairs of a chunk: the first layer (scalar input)
 // from the LDS copy of (w0, b0), then the residual hidden layers Z = W H as
 // 8 x 32 MFMA steps whose forward and tangent columns share each weight
-// fragment.  On return h[T][i], dh[T][i] hold rows 16T + drow(i, g) of
+// fragment.  On return h[T][i], dh[T][i] hold rows 16T + 4g + i of
 // column c; the result is the output-layer section of the table.  Without
 // kTan only the forward runs (dh is left untouched): the moment needs the
 // encoder output alone, so a pass 1 that keeps no workspace skips the
 // tangent's half of the products.
-template <int K, int TM, typename R, int NW, int DR, int NM, bool kTan = true>
-__device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int sj, R r,
-                                                   const R* __restrict__ tab, R (&h)[8][4], R (&dh)[8][4]) {
+template <int K, int TM, int NW, int DR, int NM, bool kTan = true>
+__device__ __forceinline__ const float* encoder_hidden(const FusedArgs& A, const Smem<K, TM, float, NW, DR, NM>& S,
+                                                       int sj, float r, const float* __restrict__ tab,
+                                                       Hidden<float>& out) {
+  typedef float R;
+  float(&h)[8][4] = out.h;
+  float(&dh)[8][4] = out.dh;
   typedef Stream<K, R> St;
   typedef typename St::vh_t vh_t;
   constexpr int NH = St::NH, VW = St::VW, kRing = St::kRing;
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int lane = phase_tid() & 63, g = lane >> 4;
   constexpr int kLayerBytes = int(kEncWidth * kEncWidth * sizeof(R));
   constexpr int kBiasBytes = int(kEncWidth * sizeof(R));
   const int nh = A.enc_hidden;
@@ -475,8 +662,8 @@ __device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Sme
   for (int T = 0; T < 8; ++T)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int in = 16 * T + drow<R>(i, g);
-      const R w0 = S.u.l0[sj][0][in], z = w0 * r + S.u.l0[sj][1][in];
+      const int in = 16 * T + hrow(i, g);
+      const R w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
       const R s = sigmoid(z);
       h[T][i] = z * s;
       if constexpr (kTan) dh[T][i] = silu_slope(z, s) * w0;
@@ -550,13 +737,16 @@ __device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Sme
 // with kTan).  Even and odd k-steps accumulate separately so 4 KT independent
 // MFMA chains are in flight; the bias is added at the end so the first
 // products do not wait for its load.
-template <int K, typename R, bool kTan = true>
-__device__ __forceinline__ void encoder_out_rows(const R* __restrict__ layer, const R (&h)[8][4], const R (&dh)[8][4],
-                                                 v4<R> (&mo)[K / 16], v4<R> (&dmo)[K / 16]) {
+template <int K, bool kTan = true>
+__device__ __forceinline__ void encoder_out_rows(const float* __restrict__ layer, const Hidden<float>& in,
+                                                 v4f (&mo)[K / 16], v4f (&dmo)[K / 16]) {
+  typedef float R;
+  const float(&h)[8][4] = in.h;
+  const float(&dh)[8][4] = in.dh;
   typedef Stream<K, R> St;
   typedef typename St::vo_t vo_t;
   constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
-  const int lane = threadIdx.x & 63, c = lane & 15;
+  const int lane = phase_tid() & 63, c = lane & 15;
   const R* __restrict__ bout = layer + K * kEncWidth;
   v4<R> mo2[2][KT], dmo2[2][KT];
   R b[KT];
@@ -598,13 +788,16 @@ __device__ __forceinline__ void encoder_out_rows(const R* __restrict__ layer, co
 // the A operand): register q of lane (g, c) for output tile Tc holds
 // m[pair c][16Tc + drow(q, g)], which is exactly the B operand of pass 2's
 // W m product.
-template <int K, typename R>
-__device__ __forceinline__ void encoder_out_cols(const R* __restrict__ layer, const R (&h)[8][4], const R (&dh)[8][4],
-                                                 R (&mB)[K / 16][4], R (&dmB)[K / 16][4]) {
+template <int K>
+__device__ __forceinline__ void encoder_out_cols(const float* __restrict__ layer, const Hidden<float>& in,
+                                                 float (&mB)[K / 16][4], float (&dmB)[K / 16][4]) {
+  typedef float R;
+  const float(&h)[8][4] = in.h;
+  const float(&dh)[8][4] = in.dh;
   typedef Stream<K, R> St;
   typedef typename St::vo_t vo_t;
   constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
-  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int lane = phase_tid() & 63, g = lane >> 4;
   const R* __restrict__ bout = layer + K * kEncWidth;
   v4<R> acc[KT], dacc[KT];
 #pragma unroll
@@ -644,32 +837,271 @@ __device__ __forceinline__ void encoder_out_cols(const R* __restrict__ layer, co
     }
 }
 
-// Pass 1 on one chunk: encoder forward, moment accumulation and, when kWs,
-// the encoder tangent and the workspace write of (m, dm).
-template <int K, int TM, typename R, int NW, int DR, int NM, bool kWs>
-__device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, int ch, const PairPos pp, R* __restrict__ wsc) {
+// Products of half a 16-row weight tile (columns 64 hf .., fragments w[7 hf ..])
+// with the digits x of 16 columns: 28 MFMAs.  With kNext each fragment's
+// registers take the fragment at next + f of the stream after its last use,
+// half a tile of products before that one is needed.  kRows: the activation
+// columns are the rows of the result.
+template <bool kRows, bool kNext>
+__device__ __forceinline__ void half_products(v4i (&w)[kTileFrags], const Digits& x, v4i (&S)[kDigits], int hf,
+                                              const FragStream<v4i>& frag, int next) {
+  if (hf == 0) {
+#pragma unroll
+    for (int i = 0; i < kDigits; ++i) S[i] = v4i{0, 0, 0, 0};
+  }
+#pragma unroll
+  for (int i = 0; i < kDigits; ++i) {
+    const int f = hf * kDigits + i;
+#pragma unroll
+    for (int j = 0; i + j < kDigits; ++j)
+      S[i + j] = kRows ? mfma_i8(x.s[j][hf], w[f], S[i + j]) : mfma_i8(w[f], x.s[j][hf], S[i + j]);
+    if constexpr (kNext) w[f] = frag[next + f];
+  }
+}
+template <bool kRows, bool kNext>
+__device__ __forceinline__ void tile_products(v4i (&w)[kTileFrags], const Digits& x, v4i (&S)[kDigits],
+                                              const FragStream<v4i>& frag, int next) {
+  half_products<kRows, kNext>(w, x, S, 0, frag, next);
+  half_products<kRows, kNext>(w, x, S, 1, frag, next);
+}
+
+// Keeps a value in accumulation registers until its next use.
+__device__ __forceinline__ void park(double& x) { asm("" : "+a"(x)); }
+
+// Order of a region that holds the 28 MFMAs of half_products and vector work:
+// kValu vector instructions after each MFMA, and with kLoads each fragment's
+// load after its last use.  A 16x16x64 integer MFMA occupies the matrix pipe
+// for 16 cycles and issue for about 9, a vector instruction issue for 4 to 5
+// (measured on one wavefront), so two vector instructions fit beside each.
+template <int kValu, bool kLoads>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+  for (int i = 0; i < kDigits; ++i) {
+#pragma unroll
+    for (int j = 0; i + j < kDigits; ++j) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+    }
+    if constexpr (kLoads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// float64: each layer's products on digits (above), one 16-row tile at a
+// time: first the activations' products, then the tangents'.  The vector work
+// that turns a tile's sums into new activations is spread over the products
+// that follow, about two instructions per MFMA.
+template <int K, int TM, int NW, int DR, int NM, bool kTan = true>
+__device__ __forceinline__ const double* encoder_hidden(const FusedArgs& A, const Smem<K, TM, double, NW, DR, NM>& S,
+                                                        int sj, double r, const double* __restrict__ tab,
+                                                        Hidden<double>& out) {
+  const int lane = phase_tid() & 63, g = lane >> 4;
+  constexpr int kFragBytes = 8 * kTileFrags * 1024;
+  const int nh = A.enc_hidden;
+  const double* __restrict__ layer = tab + 2 * kEncWidth;
+  const SigmoidConst kc;
+  double h[8][4], dh[8][4];
+#pragma unroll
+  for (int T = 0; T < 8; ++T)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int in = 16 * T + hrow(i, g);
+      const double w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
+      const double s = sigmoid(z, kc);
+      h[T][i] = z * s;
+      if constexpr (kTan) {
+        dh[T][i] = silu_slope(z, s) * w0;
+      }
+    }
+  for (int t = 1; t < nh; ++t) {
+    const FragStream<v4i> frag(layer, kFragBytes);
+    const double* __restrict__ rows = layer + kFragBytes / 8;  // row scales, then biases
+    const RowStream scale(rows, g), bias(rows + kEncWidth, g);
+    v4i w[kTileFrags];
+#pragma unroll
+    for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
+    const double dsc = digit_scale(h, out.h);
+    double dsct = 0.0;
+    if constexpr (kTan) dsct = digit_scale(dh, out.dh);
+    make_digits(h, dsc, 0, out.h);
+    v4i sf[kDigits], st[kDigits];
+    double sc[4], bi[4], z[4], slope[4];
+    auto act = [&](int T, int q) {
+      const double s = sigmoid(z[q], kc);
+      h[T][q] = fma(z[q], s, h[T][q]);
+      if constexpr (kTan) slope[q] *= silu_slope(z[q], s);
+    };
+    auto sum = [&](int q) {
+      const double rs = sc[q];
+      z[q] = fma(digit_sum(sf, q) * rs, out.h.inv, bi[q]);
+      if constexpr (kTan) slope[q] = rs * out.dh.inv;
+    };
+    auto tan_sum = [&](int T, int q) {
+      dh[T][q] = fma(slope[q], digit_sum(st, q), dh[T][q]);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int To = 0; To <= 8; ++To) {
+      const int next = (To + 1) * kTileFrags;
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        if (To < 8 && hf == 1) {
+          scale.load(To, sc);
+          bias.load(To, bi);
+        }
+        if (To < 8) half_products<false, !kTan>(w, out.h, sf, hf, frag, next);
+        if (To > 0) {
+          act(To - 1, 2 + hf);
+          if constexpr (kTan) {
+            tan_sum(To - 1, 2 * hf);
+            tan_sum(To - 1, 2 * hf + 1);
+          }
+        } else {
+          if (hf == 0) make_digits(h, dsc, 1, out.h);
+          else if constexpr (kTan) make_digits(dh, dsct, 0, out.dh);
+        }
+        if (To < 8) {
+          if (To == 0) interleave<5, !kTan>();
+          else interleave<2, !kTan>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (To == 8) continue;
+      if constexpr (kTan) {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          half_products<false, true>(w, out.dh, st, hf, frag, next);
+          if (hf == 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sum(q);
+            if (To == 0) make_digits(dh, dsct, 1, out.dh);
+          } else {
+            act(To, 0);
+            act(To, 1);
+          }
+          if (To == 0 && hf == 0) interleave<7, true>();
+          else interleave<2, true>();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum(q);
+        act(To, 0);
+        act(To, 1);
+      }
+    }
+    layer = rows + 2 * kEncWidth;
+  }
+  make_digits(h, out.h);
+  if constexpr (kTan) make_digits(dh, out.dh);
+  return layer;
+}
+
+// float64 output layer with pairs as rows: mo[Tc] register q holds
+// m[pair 4g + q][16Tc + c] (dmo the same for the tangent).
+template <int K, bool kTan = true>
+__device__ __forceinline__ void encoder_out_rows(const double* __restrict__ layer, const Hidden<double>& in,
+                                                 v4d (&mo)[K / 16], v4d (&dmo)[K / 16]) {
   constexpr int KT = K / 16;
-  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  constexpr int kFragBytes = KT * kTileFrags * 1024;
+  const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
+  const FragStream<v4i> frag(layer, kFragBytes);
+  const double* __restrict__ cols = layer + kFragBytes / 8;
+  v4i w[kTileFrags], sf[kDigits], st[kDigits];
+#pragma unroll
+  for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
+  double inv[4], dinv[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    inv[q] = __shfl(in.h.inv, hrow(q, g), 64);
+    if constexpr (kTan) dinv[q] = __shfl(in.dh.inv, hrow(q, g), 64);
+  }
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc) {
+    const double sc = cols[16 * Tc + c], b = cols[K + 16 * Tc + c];
+    tile_products<true, !kTan>(w, in.h, sf, frag, (Tc + 1) * kTileFrags);
+    if constexpr (kTan) tile_products<true, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      mo[Tc][q] = fma(digit_sum(sf, q) * sc, inv[q], b);
+      if constexpr (kTan) dmo[Tc][q] = digit_sum(st, q) * sc * dinv[q];
+    }
+  }
+}
+
+// float64 output layer with pairs as columns: register q of lane (g, c) for
+// output tile Tc holds m[pair c][16Tc + 4g + q], the B operand of pass 2's
+// W m product.
+template <int K>
+__device__ __forceinline__ void encoder_out_cols(const double* __restrict__ layer, const Hidden<double>& in,
+                                                 double (&mB)[K / 16][4], double (&dmB)[K / 16][4]) {
+  constexpr int KT = K / 16;
+  constexpr int kFragBytes = KT * kTileFrags * 1024;
+  const int lane = phase_tid() & 63, g = lane >> 4;
+  const FragStream<v4i> frag(layer, kFragBytes);
+  const double* __restrict__ rows = layer + kFragBytes / 8;
+  const RowStream scale(rows, g), bias(rows + K, g);
+  v4i w[kTileFrags], sf[kDigits], st[kDigits];
+#pragma unroll
+  for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc) {
+    double sc[4], b[4];
+    scale.load(Tc, sc);
+    bias.load(Tc, b);
+    tile_products<false, false>(w, in.h, sf, frag, 0);
+    tile_products<false, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      mB[Tc][q] = fma(digit_sum(sf, q) * sc[q], in.h.inv, b[q]);
+      dmB[Tc][q] = digit_sum(st, q) * sc[q] * in.dh.inv;
+    }
+  }
+}
+
+// Pair whose row of the float64 feature product this lane's column c = 4q + g
+// becomes: register q of the encoder's output holds pair 4g + q.
+__device__ __forceinline__ int moment_pair(int c, double) { return 4 * (c & 3) + (c >> 2); }
+__device__ __forceinline__ int moment_pair(int c, float) { return c; }
+
+// Pass 1 on one chunk: encoder forward, moment accumulation and, when kWs,
+// the encoder tangent and the workspace write of (m, dm).  Nothing but the
+// encoder's own state is held across its hidden layers: the pairs' unit
+// vectors wait in LDS, and the next chunk is taken and its positions are
+// requested (into pp) beside the output layer.
+template <int K, int TM, typename R, int NW, int DR, int NM, bool kWs>
+__device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, int ch, int nch, int* next_ch,
+                            PairPos& pp, R* __restrict__ wsc) {
+  constexpr int KT = K / 16;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  v4<R> mo[KT], dmo[KT];
+  {
+    const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
+    double dxd, dyd, dzd;
+    int atom;
+    pair_delta(A, S, ch, pp, &dxd, &dyd, &dzd, &atom);
+    const R dx = R(dxd), dy = R(dyd), dz = R(dzd);
+    const R r = vsqrt(dx * dx + dy * dy + dz * dz);
+    if (g == 0) {
+      const R ir = vrcp(r);
+      R fc, dfc_unused;
+      cutoff(r, R(A.pi_rc), &fc, &dfc_unused);
+      S.u.p1.geo[wave][c][0] = dx * ir;
+      S.u.p1.geo[wave][c][1] = dy * ir;
+      S.u.p1.geo[wave][c][2] = dz * ir;
+      S.u.p1.geo[wave][c][3] = atom < 0 ? R(0) : fc;
+    }
+    Hidden<R> hid;
+    const R* __restrict__ layer =
+        encoder_hidden<K, TM, NW, DR, NM, kWs>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
+    *next_ch = grab_chunk(&S.next_chunk[0]);
+    if (*next_ch < nch) pp = load_pair_pos(A, S, *next_ch);
+    encoder_out_rows<K, kWs>(layer, hid, mo, dmo);
+  }
+  const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
   // chunk-wide values, in scalar registers
   const int start = __builtin_amdgcn_readfirstlane(S.ch_start[ch]);
   const int count = __builtin_amdgcn_readfirstlane(S.ch_count[ch]);
-
-  double dxd, dyd, dzd;
-  int atom;
-  pair_delta(A, S, ch, pp, &dxd, &dyd, &dzd, &atom);
-  const R dx = R(dxd), dy = R(dyd), dz = R(dzd);
-  const R r = vsqrt(dx * dx + dy * dy + dz * dz);
-  const R ir = vrcp(r);
-  const R ux = dx * ir, uy = dy * ir, uz = dz * ir;
-  R fc, dfc_unused;
-  cutoff(r, R(A.pi_rc), &fc, &dfc_unused);
-  if (atom < 0) fc = R(0);
-
-  R h[8][4], dh[8][4];
-  const R* __restrict__ layer =
-      encoder_hidden<K, TM, R, NW, DR, NM, kWs>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), h, dh);
-  v4<R> mo[KT], dmo[KT];
-  encoder_out_rows<K, R, kWs>(layer, h, dh, mo, dmo);
 
   // moment: P[mm][col] += sum_pairs fc * a_mm(u) * m[pair][col], one MFMA
   // product per centre atom present in the chunk and 16-row tile of the
@@ -683,16 +1115,21 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
   v4<R> av[NA];
   int aa[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) aa[q] = __shfl(atom, drow<R>(q, g), 64);
+  for (int q = 0; q < 4; ++q) {
+    const int p = hrow(q, g);
+    aa[q] = p < count ? S.pair_a[start + p] : -1;
+  }
   {
+    const R* geo = S.u.p1.geo[wave][moment_pair(c, R(0))];
+    const R ax = geo[0], ay = geo[1], az = geo[2], fa = geo[3];
     R mono[NM];
-    monomials_n<NM, false>(ux, uy, uz, mono, mono, mono, mono);
+    monomials_n<NM, false>(ax, ay, az, mono, mono, mono, mono);
 #pragma unroll
     for (int ta = 0; ta < NA; ++ta) av[ta] = v4<R>{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < NM / 4; ++i) {
       // A[pair c][m = 4i + g] = fc m_m(u_c); B[m = 4i + g][row c] = Q[row][m]
-      const R x = fc * pick4(g, mono[4 * i], mono[4 * i + 1], mono[4 * i + 2], mono[4 * i + 3]);
+      const R x = fa * pick4(g, mono[4 * i], mono[4 * i + 1], mono[4 * i + 2], mono[4 * i + 3]);
 #pragma unroll
       for (int ta = 0; ta < NA; ++ta) av[ta] = mfma(x, S.qc[16 * ta + c][4 * i + g], av[ta]);
     }
@@ -724,13 +1161,13 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
 
   if (kWs) {
     // workspace in the B-operand order pass 2 loads, contiguous per lane:
-    // lane 16 g' + c' holds m[pair c'][16Tc + drow(i, g')] at 4 KT lane' +
+    // lane 16 g' + c' holds m[pair c'][16Tc + 4g' + i] at 4 KT lane' +
     // 4 Tc + i (then the same for dm)
 #pragma unroll
     for (int Tc = 0; Tc < KT; ++Tc)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int off = (16 * gof<R>(c) + drow<R>(q, g)) * (4 * KT) + Tc * 4 + qof<R>(c);
+        const int off = (16 * (c >> 2) + hrow(q, g)) * (4 * KT) + Tc * 4 + (c & 3);
         wsc[off] = mo[Tc][q];
         wsc[K * 16 + off] = dmo[Tc][q];
       }
@@ -751,7 +1188,7 @@ __device__ __forceinline__ void pass2_load(const FusedArgs& A, const Smem<K, TM,
   constexpr int VW = 16 / int(sizeof(R));
   constexpr int NV = K / 4 / VW;  // 16-byte loads per lane for m (and for dm)
   typedef R vw_t __attribute__((ext_vector_type(VW)));
-  const int lane = threadIdx.x & 63;
+  const int lane = phase_tid() & 63;
   const vw_t* __restrict__ pm = reinterpret_cast<const vw_t*>(wsc + lane * (K / 4));
   const vw_t* __restrict__ pd = reinterpret_cast<const vw_t*>(wsc + K * 16 + lane * (K / 4));
   vw_t vm[NV], vd[NV];
@@ -780,9 +1217,9 @@ __device__ __forceinline__ void pass2_recompute(const FusedArgs& A, const Smem<K
   pair_delta(A, S, ch, pp, &dxd, &dyd, &dzd, &atom);
   const R dx = R(dxd), dy = R(dyd), dz = R(dzd);
   const R r = vsqrt(dx * dx + dy * dy + dz * dz);
-  R h[8][4], dh[8][4];
-  const R* __restrict__ layer = encoder_hidden(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), h, dh);
-  encoder_out_cols<K, R>(layer, h, dh, in.mB, in.dmB);
+  Hidden<R> hid;
+  const R* __restrict__ layer = encoder_hidden<K, TM, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
+  encoder_out_cols<K>(layer, hid, in.mB, in.dmB);
   in.pp = pp;
 }
 
@@ -814,7 +1251,7 @@ __device__ __forceinline__ void scatter_fj_tile(const FusedArgs& A, Smem<K, TM, 
 template <int K, int TM, typename R, int NW, int DR, int NM, bool kTileFj = false>
 __device__ void pass2_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, int ch, const Pass2In<K, R>& in) {
   constexpr int KT = K / 16;
-  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
   // chunk-wide values, in scalar registers
   const int start = __builtin_amdgcn_readfirstlane(S.ch_start[ch]);
   const int count = __builtin_amdgcn_readfirstlane(S.ch_count[ch]);
@@ -855,7 +1292,7 @@ __device__ void pass2_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           constexpr int DRS = moment_rows(DR, NM);
-          const R w = 16 * ta + 16 <= DRS || 16 * ta + c < DRS ? S.P[a][16 * ta + c][16 * Tc + drow<R>(i, g)] : R(0);
+          const R w = 16 * ta + 16 <= DRS || 16 * ta + c < DRS ? S.P[a][16 * ta + c][16 * Tc + hrow(i, g)] : R(0);
           t1 = mfma(w, in.mB[Tc][i], t1);
           t2 = mfma(w, in.dmB[Tc][i], t2);
         }
@@ -948,17 +1385,17 @@ __device__ void pass2_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
 template <int K, int TM, typename R, int NW, int DR, int NM>
 __device__ void radial_chunk(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int ch) {
   constexpr int KT = K / 16;
-  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
   const bool valid = c < S.ch_count[ch];
   const long long e = S.row_beg[0] + (valid ? S.pair_j[S.ch_start[ch] + c] : 0);
   const R r = valid ? R(A.geo[4 * e + 3]) : R(1);
   R fc, dfc;
   cutoff(r, R(A.pi_rc), &fc, &dfc);
   if (!valid) fc = dfc = R(0);
-  R h[8][4], dh[8][4];
-  const R* __restrict__ layer = encoder_hidden(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), h, dh);
+  Hidden<R> hid;
+  const R* __restrict__ layer = encoder_hidden<K, TM, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
   R mB[KT][4], dmB[KT][4];
-  encoder_out_cols<K, R>(layer, h, dh, mB, dmB);
+  encoder_out_cols<K>(layer, hid, mB, dmB);
   if (valid) {
     R* __restrict__ gr = static_cast<R*>(A.grad) + e * K;
     R* __restrict__ gp = static_cast<R*>(A.gprime) + e * K;
@@ -966,7 +1403,7 @@ __device__ void radial_chunk(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM
     for (int Tc = 0; Tc < KT; ++Tc)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int col = 16 * Tc + drow<R>(q, g);
+        const int col = 16 * Tc + hrow(q, g);
         gr[col] = fc * mB[Tc][q];
         gp[col] = dfc * mB[Tc][q] + fc * dmB[Tc][q];
       }
@@ -1018,7 +1455,7 @@ __device__ __forceinline__ HeadGroup<R> head_group(int G, bool rw, int w, int nw
                                                    const R* __restrict__ hid) {
   constexpr int RW = kHeadWidth;
   constexpr int HS = 2 * RW * RW + RW;
-  const int lane = threadIdx.x & 63;
+  const int lane = phase_tid() & 63;
   const int tin = nin / 16, k0 = nin / 4, nl0 = (k0 + 15) / 16;
   if (rw) {
     if (G < nl0) return {A0f + (64 * G + w) * 64 + lane, 4, k0 - 16 * G < 16 ? k0 - 16 * G : 16};
@@ -1056,7 +1493,8 @@ __device__ void head_stage(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S) {
   constexpr int HS = 2 * RW * RW + RW;  // one hidden layer: A_t and A_t^T fragments, c_t
   constexpr int NC = TM > 16 ? 32 : 16;  // atom columns: one or two groups of 16
   constexpr int CG = NC / 16;
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15, w = tid >> 6;
+  const int tid = phase_tid(), lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int na = S.na;
   const int nin = (A.lmax + 1) * K;
   const int tin = nin / 16;
@@ -1261,7 +1699,7 @@ __device__ __forceinline__ void stage_first_layer(const FusedArgs& A, Smem<K, TM
     const int sj = u / (2 * kEncWidth), rem = u % (2 * kEncWidth);
     const int si = S.tile_species;
     const int tau = A.enc_cond == 2 ? si * A.C + sj : (A.enc_cond == 1 ? sj : 0);
-    S.u.l0[sj][rem / kEncWidth][rem % kEncWidth] = enc[(long long)tau * A.enc_stride + rem];
+    S.u.p1.l0[sj][rem / kEncWidth][rem % kEncWidth] = enc[(long long)tau * A.enc_stride + rem];
   }
 }
 
@@ -1280,14 +1718,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
   static_assert(TM <= 64, "the bucket table gives one lane to each atom of a tile");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Smem<K, TM, R, NW, DR, NM>& S = *reinterpret_cast<Smem<K, TM, R, NW, DR, NM>*>(smem_raw);
-  const int tid = threadIdx.x, wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const long long chunk_elems = 2LL * K * 16;
   R* __restrict__ ws_slot = static_cast<R*>(A.ws) + (long long)blockIdx.x * A.ws_slot;
   const R* __restrict__ enc = static_cast<const R*>(A.enc);
   const R* __restrict__ qc = static_cast<const R*>(A.qc);
 
-  for (int u = tid; u < DR * NM; u += (64 * NW)) S.qc[u / NM][u % NM] = qc[u];
-  for (int u = tid; u < DR; u += 64 * NW) S.rw[u] = qc[DR * NM + u];
+  for (int u = threadIdx.x; u < DR * NM; u += (64 * NW)) S.qc[u / NM][u % NM] = qc[u];
+  for (int u = threadIdx.x; u < DR; u += 64 * NW) S.rw[u] = qc[DR * NM + u];
 
   // XCD-aware assignment: blocks are dispatched round-robin over the 8 XCDs,
   // so block b works on the b%8-th contiguous eighth of the tile list and
@@ -1303,6 +1741,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
     // neighbour list, and each row is grouped by neighbour species, so the
     // bucket position of an entry follows from a block-wide prefix count of
     // active entries; every thread handles 8 consecutive entries.
+    const int tid = phase_tid();
     if (tid == 0) {
       int s = 0;
       while (s + 1 < A.C && tile >= A.tile_start[s + 1]) ++s;
@@ -1489,12 +1928,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
     } else {
       constexpr bool kWs = MODE == kCached || MODE == kCachedTileFj || MODE == kDerive;
       int ch = wave;
-      PairPos next = ch < nch ? load_pair_pos(A, S, ch) : PairPos{0.0, 0.0, 0.0};
+      PairPos pp = ch < nch ? load_pair_pos(A, S, ch) : PairPos{0.0, 0.0, 0.0};
       while (ch < nch) {
-        const PairPos cur = next;
-        const int ch2 = grab_chunk(&S.next_chunk[0]);
-        if (ch2 < nch) next = load_pair_pos(A, S, ch2);
-        pass1_chunk<K, TM, R, NW, DR, NM, kWs>(A, S, ch, cur, ws_slot + ch * chunk_elems);
+        int ch2;
+        pass1_chunk<K, TM, R, NW, DR, NM, kWs>(A, S, ch, nch, &ch2, pp, ws_slot + ch * chunk_elems);
         ch = ch2;
       }
     }
@@ -1532,13 +1969,16 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
         __syncthreads();
       }
       // inputs of the next chunk are loaded while this one is processed
+      // (float64 at k = 64: two chunks' inputs alone are 256 registers)
+      constexpr bool kAhead = K * sizeof(R) <= 256;
       int ch = wave;
       Pass2In<K, R> next;
-      if (ch < nch) pass2_load(A, S, ch, ws_slot + ch * chunk_elems, next);
+      if (kAhead && ch < nch) pass2_load(A, S, ch, ws_slot + ch * chunk_elems, next);
       while (ch < nch) {
+        if (!kAhead) pass2_load(A, S, ch, ws_slot + ch * chunk_elems, next);
         const Pass2In<K, R> cur = next;
         const int ch2 = grab_chunk(&S.next_chunk[1]);
-        if (ch2 < nch) pass2_load(A, S, ch2, ws_slot + ch2 * chunk_elems, next);
+        if (kAhead && ch2 < nch) pass2_load(A, S, ch2, ws_slot + ch2 * chunk_elems, next);
         pass2_chunk<K, TM, R, NW, DR, NM, kTileFj>(A, S, ch, cur);
         ch = ch2;
       }
@@ -1626,6 +2066,7 @@ hipError_t launch_k(const FusedArgs& a, int n_blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
+#if MLIP_FUSED_PART != 2
 template <int K, int TM, typename R, int NW, int DR, int NM>
 hipError_t launch_mode(int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
   switch (mode) {
@@ -1639,9 +2080,11 @@ hipError_t launch_mode(int mode, const FusedArgs& a, int n_blocks, hipStream_t s
     default: return hipErrorInvalidValue;
   }
 }
+#endif
 
 }  // namespace
 
+#if MLIP_FUSED_PART == 1
 // Angular configurations: 0 = irreducible basis with l_max <= 3 (16 rows,
 // 20 monomials), 1 = Cartesian basis with l_max <= 3 (20 rows in two 16-row
 // tiles), 2 = irreducible basis with l_max 4 or 5 (up to 36 rows in three
@@ -1675,40 +2118,44 @@ int fused_tile_max(int k, int precision, int acfg) {
 hipError_t launch_fused(int k, int precision, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
   if (mode != kCached && (k != 32 || acfg != 0)) return hipErrorInvalidValue;
   if (acfg == 1 && k != 32) return hipErrorInvalidValue;
-  if (precision == 64) {
-    if (acfg == 1) return launch_k<32, 16, double, 4, 32, 20, kCached>(a, n_blocks, s);
-    if (acfg == 2) {
-      switch (k) {
-        case 16: return launch_k<16, 16, double, 4, 48, 56, kCached>(a, n_blocks, s);
-        case 32: return launch_k<32, 9, double, 4, 48, 56, kCached>(a, n_blocks, s);
-        case 64: return launch_k<64, 3, double, 4, 48, 56, kCached>(a, n_blocks, s);
-        default: return hipErrorInvalidValue;
-      }
-    }
+  if (precision == 32) return launch_fused_f32(k, acfg, mode, a, n_blocks, s);
+  if (precision != 64) return hipErrorInvalidValue;
+  if (acfg == 2) return launch_fused_f64_high(k, a, n_blocks, s);
+  if (acfg == 1) return launch_k<32, 16, double, 4, 32, 20, kCached>(a, n_blocks, s);
+  switch (k) {
+    case 16: return launch_k<16, 16, double, 4, 16, 20, kCached>(a, n_blocks, s);
+    case 32: return launch_mode<32, 16, double, 4, 16, 20>(mode, a, n_blocks, s);
+    case 64: return launch_k<64, 8, double, 4, 16, 20, kCached>(a, n_blocks, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+#elif MLIP_FUSED_PART == 2
+hipError_t launch_fused_f64_high(int k, const FusedArgs& a, int n_blocks, hipStream_t s) {
+  switch (k) {
+    case 16: return launch_k<16, 16, double, 4, 48, 56, kCached>(a, n_blocks, s);
+    case 32: return launch_k<32, 9, double, 4, 48, 56, kCached>(a, n_blocks, s);
+    case 64: return launch_k<64, 3, double, 4, 48, 56, kCached>(a, n_blocks, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+#elif MLIP_FUSED_PART == 3
+hipError_t launch_fused_f32(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
+  if (acfg == 1) return launch_k<32, 32, float, 8, 32, 20, kCached>(a, n_blocks, s);
+  if (acfg == 2) {
     switch (k) {
-      case 16: return launch_k<16, 16, double, 4, 16, 20, kCached>(a, n_blocks, s);
-      case 32: return launch_mode<32, 16, double, 4, 16, 20>(mode, a, n_blocks, s);
-      case 64: return launch_k<64, 8, double, 4, 16, 20, kCached>(a, n_blocks, s);
-      default: break;
-    }
-  } else if (precision == 32) {
-    if (acfg == 1) return launch_k<32, 32, float, 8, 32, 20, kCached>(a, n_blocks, s);
-    if (acfg == 2) {
-      switch (k) {
-        case 16: return launch_k<16, 32, float, 8, 48, 56, kCached>(a, n_blocks, s);
-        case 32: return launch_k<32, 16, float, 8, 48, 56, kCached>(a, n_blocks, s);
-        case 64: return launch_k<64, 11, float, 8, 48, 56, kCached>(a, n_blocks, s);
-        default: return hipErrorInvalidValue;
-      }
-    }
-    switch (k) {
-      case 16: return launch_k<16, 32, float, 8, 16, 20, kCached>(a, n_blocks, s);
-      case 32: return launch_mode<32, 32, float, 8, 16, 20>(mode, a, n_blocks, s);
-      case 64: return launch_k<64, 16, float, 8, 16, 20, kCached>(a, n_blocks, s);
-      default: break;
+      case 16: return launch_k<16, 32, float, 8, 48, 56, kCached>(a, n_blocks, s);
+      case 32: return launch_k<32, 16, float, 8, 48, 56, kCached>(a, n_blocks, s);
+      case 64: return launch_k<64, 11, float, 8, 48, 56, kCached>(a, n_blocks, s);
+      default: return hipErrorInvalidValue;
     }
   }
-  return hipErrorInvalidValue;
+  switch (k) {
+    case 16: return launch_k<16, 32, float, 8, 16, 20, kCached>(a, n_blocks, s);
+    case 32: return launch_mode<32, 32, float, 8, 16, 20>(mode, a, n_blocks, s);
+    case 64: return launch_k<64, 16, float, 8, 16, 20, kCached>(a, n_blocks, s);
+    default: return hipErrorInvalidValue;
+  }
 }
+#endif
 
 }  // namespace mlip

@@ -32,8 +32,15 @@ constexpr int kMonomials = 20;            // Cartesian monomials of degree <= 3
 constexpr size_t kStaticScratchBytes = size_t(256) << 20;
 constexpr size_t kStaticScratchHeader = 256;
 
-// Number of values in one packed encoder table (device layout).
-inline size_t enc_table_elems(int k, int enc_hidden) {
+// Base-256 digits of a float64 encoder weight on the device (fused.hip).
+constexpr int kWeightDigits = 7;
+// Number of values in one packed encoder table (device layout).  float64
+// tables hold each weight matrix as digits, seven bytes per weight, with a
+// scale per row beside the bias.
+inline size_t enc_table_elems(int k, int enc_hidden, int precision) {
+  if (precision == 64)
+    return 2 * kEncWidth + size_t(enc_hidden - 1) * (kEncWidth * kEncWidth / 8 * kWeightDigits + 2 * kEncWidth) +
+           size_t(k) * kEncWidth / 8 * kWeightDigits + 2 * size_t(k);
   return 2 * kEncWidth + size_t(enc_hidden - 1) * (kEncWidth * kEncWidth + kEncWidth) +
          size_t(k) * kEncWidth + k;
 }
@@ -256,6 +263,9 @@ int angular_config(int angular, int lmax);
 void angular_table_shape(int acfg, int* rows, int* cols);
 int fused_tile_max(int k, int precision, int acfg);  // centre atoms per tile of that instantiation
 hipError_t launch_fused(int k, int precision, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
+// its parts (one object each): float64 with l_max 4..5, and float32
+hipError_t launch_fused_f64_high(int k, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f32(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
 // Modes of launch_fused used by the unfused configuration.
 constexpr int kModeRegress = 3;   // Eq. 6: G -> E_i, dE/dG
 constexpr int kModeRadial = 5;    // Eq. 2: distances -> g_rad, dg_rad/dr per entry

@@ -1,0 +1,102 @@
+"""The encoder's float64 products on 8-bit integer digits (csrc/fused.hip):
+weights and activations at the ends of what the digits hold - all zero, all
+digits at their extreme, rows of very different size, exponents far from one -
+and weights that are not finite.
+
+Bound: a product's rounding is below 128 x 2^-53 of (largest weight of the
+row) x (largest activation of the column), 1.4e-14; the outputs pass through
+three such layers and sums of partial forces that cancel by at most about ten,
+so they agree with the oracle to 1e-12 of an output's largest value."""
+import numpy as np
+import pytest
+
+import synth
+from oracle.model import Model, evaluate
+from tests.gpu_helpers import gpu_eval, log
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+def _edit(hp, weights, change):
+    """Blob with change(name, values) applied to each segment."""
+    out, pos = np.array(weights, copy=True), 0
+    for name, n, _ in synth.weight_segments(hp):
+        change(name, out[pos:pos + n])
+        pos += n
+    return out
+
+
+def _zero_columns(name, v):
+    # a zero first layer gives zero activations, so the digits of a whole chunk are zero
+    if name.startswith("enc1.") and name[5:] in ("w0", "b0"):
+        v[:] = 0.0
+
+
+def _zero_rows(name, v):
+    if name.startswith("enc") and name.endswith(".W1"):
+        v.reshape(128, 128)[::3] = 0.0
+    if name.startswith("enc") and name.endswith(".Wout"):
+        v.reshape(-1, 128)[1::4] = 0.0
+
+
+def _extreme_digits(name, v):
+    # equal weights of 128/255 = 0.808080...(256) of a row's top, and one top
+    # value: every digit of the others is at its most negative
+    if name.startswith("enc") and (name.endswith(".W1") or name.endswith(".W2")):
+        v[:] = -(128.0 / 255.0) / 64.0
+        v.reshape(128, 128)[:, 5] = 0.99 / 64.0
+
+
+def _uneven_rows(name, v):
+    if name.startswith("enc") and name.endswith(".W1"):
+        v.reshape(128, 128)[:] *= (10.0 ** np.linspace(-12.0, 1.0, 128))[:, None]
+
+
+def _far_exponents(name, v):
+    # activations of 1e100, weights that bring them back
+    if not name.startswith("enc"):
+        return
+    if name[5:] in ("w0", "b0"):
+        v *= 1e100
+    elif name.endswith(".W1") or name.endswith(".W2") or name.endswith(".Wout"):
+        v *= 1e-100
+
+
+@pytest.mark.parametrize("change", [_zero_columns, _zero_rows, _extreme_digits, _uneven_rows, _far_exponents],
+                         ids=lambda f: f.__name__[1:])
+@pytest.mark.parametrize("k,fusion", [(16, 0), (32, 0), (32, 1), (64, 0)])
+def test_digits_match_oracle(change, k, fusion):
+    w = synth.make_workload("fcc-binary-4", seed=31, hp_overrides={"k": k})
+    weights = _edit(w.hp, w.weights, change)
+    log(f"[digits] {change.__name__} k={k} fusion={fusion}")
+    ref = evaluate(Model(w.hp, weights), w.pos, w.types, w.box)
+    got = gpu_eval(w.hp, weights, w.pos, w.types, w.box, fusion=fusion)
+    got["pot"].close()
+    for key in ("E_i", "F", "virial"):
+        scale = np.abs(ref[key]).max()
+        assert np.isfinite(scale) and scale > 0
+        err = np.abs(got[key] - ref[key]).max() / scale
+        log(f"[digits] {change.__name__} k={k} {key}: {err:.2e}")
+        assert err <= TOL, (key, err)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("segment", ["enc3.W1", "enc3.Wout", "enc3.w0"])
+def test_non_finite_weights_show(bad, segment):
+    """A NaN or infinite weight of the table of pairs (1, 1) makes the energy of
+    every atom of species 1 non-finite and leaves species 0 alone."""
+    w = synth.make_workload("fcc-binary-4", seed=32)
+
+    def change(name, v):
+        if name == segment:
+            v[7] = bad
+    weights = _edit(w.hp, w.weights, change)
+    log(f"[digits] {segment} {bad}")
+    got = gpu_eval(w.hp, weights, w.pos, w.types, w.box)
+    got["pot"].close()
+    clean = evaluate(Model(w.hp, w.weights), w.pos, w.types, w.box)
+    one = w.types == 1
+    assert not np.isfinite(got["E_i"][one]).any()
+    assert np.abs(got["E_i"][~one] - clean["E_i"][~one]).max() <= 1e-9
