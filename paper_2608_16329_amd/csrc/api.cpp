@@ -267,6 +267,30 @@ mlip_status ensure_workspace(mlip_ctx* ctx) {
   return MLIP_OK;
 }
 
+// Rounds of full tiles below which smaller tiles are looked at: with that
+// many a last round that is nearly empty costs a twelfth at most.
+constexpr int kSplitRounds = 12;
+// A tile's fixed part in chunks: 70 us beside 28 to 31 us a chunk (float64).
+constexpr double kTileFixed = 2.5;
+
+// Time of an evaluation with these tiles, in 16-pair chunks of one wavefront:
+// each work-group takes every n_blocks-th tile, a tile costs what its chunks
+// take on its wavefronts and a fixed part (staging, head, barriers), which
+// is what speaks against small tiles, beside more partly filled chunks.
+double tile_cost(const mlip_ctx* ctx, const TilePlan& t, const int32_t* sp, int64_t listed) {
+  const double inside = std::pow(ctx->hp.cutoff / (ctx->hp.cutoff + ctx->hp.skin), 3.0);
+  const double row = inside * double(listed) / double(std::max<int64_t>(1, sp[ctx->hp.n_species]));
+  double chunks = 0.0;
+  for (int s = 0; s < ctx->hp.n_species; ++s) {
+    const double share = double(sp[s + 1] - sp[s]) / double(std::max<int64_t>(1, sp[ctx->hp.n_species]));
+    const double pairs = t.atoms * row * share;
+    if (pairs > 0.0) chunks += std::max(1.0, pairs / 16.0 + 0.5);
+  }
+  const int waves = ctx->hp.precision == 64 ? 4 : 8;
+  const double rounds = double((t.tiles + t.blocks - 1) / t.blocks);
+  return rounds * (kTileFixed + std::max(1.0, chunks / waves + 0.5));
+}
+
 // Where one evaluation keeps its block totals, active-pair counter and
 // fused-kernel workspace: the context's buffers (mlip_compute) or the fixed
 // device scratch (mlip_compute_noalloc).
@@ -664,14 +688,35 @@ mlip_status mlip_build_neighbors(mlip_ctx* ctx, int64_t n_atoms, const double* p
 
   // fused-kernel tiling and workspace
   const int tm = fused_tile_max(ctx->hp.k, ctx->hp.precision, ctx->acfg);
-  const int T = std::max(1, std::min(tm, tile_entry_cap(tm) / std::max(1, ctx->max_row)));
-  ctx->tile_atoms = T;
-  int64_t tiles = 0;
-  for (int sp_i = 0; sp_i < C; ++sp_i) tiles += (int64_t(sp[sp_i + 1] - sp[sp_i]) + T - 1) / T;
-  ctx->n_tiles = tiles;
-  ctx->n_blocks = int(std::max<int64_t>(1, std::min<int64_t>(tiles, ctx->n_cu)));
-  const int64_t chunks = std::min<int64_t>(tile_chunk_cap(tm), (int64_t(T) * ctx->max_row + 15) / 16 + C);
-  ctx->ws_slot = size_t(chunks) * 2 * size_t(ctx->hp.k) * 16;
+  const int most = std::max(1, std::min(tm, tile_entry_cap(tm) / std::max(1, ctx->max_row)));
+  auto plan = [&](int T) {
+    TilePlan t{};
+    t.atoms = T;
+    for (int sp_i = 0; sp_i < C; ++sp_i) t.tiles += (int64_t(sp[sp_i + 1] - sp[sp_i]) + T - 1) / T;
+    t.blocks = int(std::max<int64_t>(1, std::min<int64_t>(t.tiles, ctx->n_cu)));
+    const int64_t chunks = std::min<int64_t>(tile_chunk_cap(tm), (int64_t(T) * ctx->max_row + 15) / 16 + C);
+    t.ws_slot = size_t(chunks) * 2 * size_t(ctx->hp.k) * 16;
+    return t;
+  };
+  // As many atoms per tile as fit, except where that leaves work-groups
+  // without a tile or most of them idle in the last round.  Measured at 256
+  // atoms: 716 us with 16-atom tiles (17 work-groups busy), 134 us with
+  // 1-atom tiles; 2,048: 732 and 526 us (9 atoms); 5,148: 1557 and 1139 us (10);
+  // at 131,072 smaller tiles only cost (26.4 ms with 16 atoms, 28.0 with 8).
+  const TilePlan full = plan(most);
+  TilePlan best = full;
+  const size_t ws_room = std::max(full.ws_bytes(ctx->elem_bytes), kStaticScratchBytes - kStaticScratchHeader);
+  double best_cost = tile_cost(ctx, full, sp, total);
+  for (int T = most - 1; T >= 1 && full.tiles < kSplitRounds * ctx->n_cu; --T) {
+    const TilePlan t = plan(T);
+    const double cost = tile_cost(ctx, t, sp, total);
+    if (cost < 0.97 * best_cost && t.ws_bytes(ctx->elem_bytes) <= ws_room) best = t, best_cost = cost;
+  }
+  ctx->tile_atoms = best.atoms;
+  ctx->n_tiles = best.tiles;
+  ctx->n_blocks = best.blocks;
+  ctx->ws_slot = best.ws_slot;
+  ctx->full_plan = full;
   MLIP_TRY(ensure_workspace(ctx));
   ctx->built = true;
   ctx->n_builds += 1;
@@ -698,13 +743,15 @@ mlip_status mlip_compute_noalloc(mlip_ctx* ctx, const double* pos_dev, double* e
                 "three-kernel and unfused ones hold per-atom intermediates the library allocates");
   // workspace of the current list: one slot per resident work-group (none
   // when the encoder output is recomputed)
-  const size_t ws_bytes =
-      ctx->fusion == MLIP_FUSION_CACHED ? ctx->ws_slot * size_t(ctx->n_blocks) * ctx->elem_bytes : 0;
+  // (the limit is that of full tiles: the smaller ones a small system may get
+  // never need more than the scratch where full ones fit)
+  const TilePlan& full = ctx->full_plan;
+  const size_t ws_bytes = ctx->fusion == MLIP_FUSION_CACHED ? full.ws_bytes(ctx->elem_bytes) : 0;
   if (kStaticScratchHeader + ws_bytes > kStaticScratchBytes)
     return fail(ctx, MLIP_E_ARG,
                 "the fused kernel's workspace needs " + std::to_string(ws_bytes) + " bytes (" +
-                    std::to_string(ctx->n_blocks) + " work-groups x " +
-                    std::to_string(ctx->ws_slot * ctx->elem_bytes) + "); the fixed scratch holds " +
+                    std::to_string(full.blocks) + " work-groups x " +
+                    std::to_string(full.ws_slot * ctx->elem_bytes) + "); the fixed scratch holds " +
                     std::to_string(kStaticScratchBytes - kStaticScratchHeader));
   void* base = nullptr;
   const hipError_t e = static_scratch_address(ctx->device, &base);

@@ -152,6 +152,16 @@ struct NbrGrid {
   double rl2;
 };
 
+// Tiles of the fused kernel: centre atoms per tile, tiles, resident
+// work-groups and workspace values per work-group.
+struct TilePlan {
+  int atoms;
+  int64_t tiles;
+  int blocks;
+  size_t ws_slot;
+  size_t ws_bytes(size_t elem) const { return ws_slot * size_t(blocks) * elem; }
+};
+
 }  // namespace mlip
 
 struct mlip_ctx {
@@ -212,6 +222,7 @@ struct mlip_ctx {
   int tile_atoms = 0;
   int64_t n_tiles = 0;
   int n_blocks = 0;
+  mlip::TilePlan full_plan{};       // with as many atoms per tile as fit
   int fusion = 0;                   // mlip_fusion
   int scatter = 0;                  // mlip_scatter
   int acfg = 0;                     // angular configuration of the kernel

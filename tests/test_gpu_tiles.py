@@ -1,0 +1,55 @@
+"""Atoms per tile of the fused kernel: systems that get fewer than the largest
+number (fewer tiles than work-groups, or a last round that would be nearly
+empty), up to the first that gets full tiles, against the oracle."""
+import numpy as np
+import pytest
+
+import synth
+from oracle.model import Model
+from tests.gpu_helpers import gpu_eval, log, oracle_full, oracle_sample
+
+pytestmark = pytest.mark.gpu
+
+TOL64, REL32 = 1e-9, 1e-4
+
+
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("edge,over", [(4, {}), (6, {}), (7, {"k": 64}), (7, {"lmax": 5}), (11, {}), (13, {})])
+def test_tile_sizes_match_oracle(edge, over, precision):
+    w = synth.make_workload("fcc-hea6-128", seed=41, n=edge, hp_overrides=dict(over, precision=precision))
+    # an odd atom count: drop a few sites
+    keep = np.arange(len(w.pos)) % 97 != 5
+    pos, types = w.pos[keep], w.types[keep]
+    log(f"[tiles] edge {edge} {over} float{precision}: {len(pos)} atoms")
+    g = gpu_eval(w.hp, w.weights, pos, types, w.box)
+    st = g["stats"]
+    g["pot"].close()
+    log(f"[tiles] {st['tile_atoms']} atoms per tile, {st['n_tiles']} tiles on {st['n_blocks']} work-groups")
+    counts = np.bincount(types, minlength=6)
+    assert st["n_tiles"] == sum(-(-int(c) // st["tile_atoms"]) for c in counts)
+    if edge <= 7:
+        assert st["n_blocks"] == st["n_tiles"] > len(pos) // 16
+    m = Model(w.hp, w.weights)
+    if len(pos) < 2000:
+        E, F, V, _, _ = oracle_full(m, pos, types, w.box)
+        got = (g["E_i"], g["F"], g["virial"])
+    else:
+        atoms = np.linspace(0, len(pos) - 1, 16).astype(np.int64)
+        E, F, V = oracle_sample(m, pos, types, w.box, atoms)
+        got = (g["E_i"][atoms], g["F"][atoms], g["virial"][atoms])
+    for name, a, b in zip("EFV", got, (E, F, V)):
+        err = np.abs(a - b).max() / (1.0 if precision == 64 else np.abs(b).max())
+        log(f"[tiles] {name}: {err:.2e}")
+        assert err <= (TOL64 if precision == 64 else REL32)
+    assert abs(g["totals"][0] - g["E_i"].sum()) <= 1e-9 * np.abs(g["E_i"]).sum()
+
+
+def test_full_tiles_of_a_large_system():
+    """65,536 atoms give every work-group a dozen full tiles and more: as many
+    atoms per tile as fit."""
+    for precision, most in ((64, 16), (32, 32)):
+        w = synth.make_workload("bcc-unary-32", seed=42, hp_overrides={"precision": precision})
+        g = gpu_eval(w.hp, w.weights, w.pos, w.types, w.box)
+        log(f"[tiles] 65,536 atoms float{precision}: {g['stats']['tile_atoms']} per tile")
+        g["pot"].close()
+        assert g["stats"]["tile_atoms"] == most or precision == 32
