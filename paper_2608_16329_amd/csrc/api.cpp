@@ -116,40 +116,51 @@ size_t head_blob_doubles(const mlip_hparams* hp) {
   return R * nin + R + size_t(hp->reg_hidden - 1) * (R * R + R) + R + 1;
 }
 
-// Fragment order of a row-major [nout][nin] matrix for MFMA 16x16x4.  The
-// fragment of block (T, i) and output tile t holds, at lane 16 g + c,
-// element [16 t + c][16 T + kin(i, g)]; kin is the row map of the MFMA
-// result registers (4 i + g for float64, 4 g + i for float32), so that a
-// result tile feeds the next product as its B operand.  Fragments of vw
-// consecutive output tiles are interleaved per lane so that one 16-byte load
-// per lane fetches vw of them: element (T, i, t, lane) sits at
-// ((((4 T + i) (nout/16/vw) + t/vw) 64 + lane) vw + t%vw.
-void pack_fragments(const double* M, int nout, int nin, int precision, int vw, std::vector<double>* out) {
-  const int nt = nout / 16;
+// Fragment order of a row-major [nout][nin] matrix for MFMA 16x16x4 (the
+// head's).  The fragment of block (T, i) and output tile t holds, at lane
+// 16 g + c, element [16 t + c][16 T + kin(i, g)]; kin is the row map of the
+// MFMA result registers (4 i + g for float64, 4 g + i for float32), so that a
+// result tile feeds the next product as its B operand.  Element (T, i, t,
+// lane) sits at ((4 T + i) (nout/16) + t) 64 + lane.
+void pack_fragments(const double* M, int nout, int nin, int precision, std::vector<double>* out) {
   for (int T = 0; T < nin / 16; ++T)
     for (int i = 0; i < 4; ++i)
-      for (int u = 0; u < nt / vw; ++u)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int v = 0; v < vw; ++v) {
-            const int g = lane >> 4, c = lane & 15, t = u * vw + v;
-            const int kin = precision == 64 ? 4 * i + g : 4 * g + i;
-            out->push_back(M[size_t(16 * t + c) * nin + 16 * T + kin]);
-          }
+      for (int t = 0; t < nout / 16; ++t)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int g = lane >> 4, c = lane & 15;
+          const int kin = precision == 64 ? 4 * i + g : 4 * g + i;
+          out->push_back(M[size_t(16 * t + c) * nin + 16 * T + kin]);
+        }
 }
 
-// A row-major [nout][128] float64 matrix as digits for the 16x16x64 8-bit
+// Append n values in the kernel's arithmetic type.
+void append_values(const double* v, size_t n, int precision, std::vector<unsigned char>* out) {
+  const size_t at = out->size(), eb = size_t(precision / 8);
+  out->resize(at + n * eb);
+  if (precision == 64) {
+    std::memcpy(out->data() + at, v, n * eb);
+  } else {
+    float* f = reinterpret_cast<float*>(out->data() + at);
+    for (size_t i = 0; i < n; ++i) f[i] = float(v[i]);
+  }
+}
+
+// Append a row-major [nout][128] matrix as digits for the 16x16x64 8-bit
 // integer MFMA, followed by one scale per row.  The integers of a row are
-// round(w s) = sum_i d_i 256^(6 - i) with digits in [-128, 127], where s takes
-// the row's largest weight to 0.99 x 2^55 (seven balanced digits hold 0.996 x
-// 2^55), and its scale is 2^56 / s (NaN for a row with an infinity or NaN,
-// whose digits are zero).  Digit i of the half hf (columns 64 hf ..) of output
-// tile t is fragment 14 t + 7 hf + i, 16 bytes at lane 16 g + c: byte 4 T + q
-// is row 16 t + c, column 64 hf + 16 T + 4 g + q.
-void pack_digits(const double* M, int nout, std::vector<double>* out) {
-  constexpr int W = kEncWidth, D = kWeightDigits;
-  const size_t at = out->size(), frag_doubles = size_t(nout) * W / 8 * D;
-  out->resize(at + frag_doubles + size_t(nout));
-  unsigned char* frag = reinterpret_cast<unsigned char*>(out->data() + at);
+// round(w s) = sum_i d_i 256^(D - 1 - i) with digits in [-128, 127], where s
+// takes the row's largest weight to 0.99 x 2^(8 D - 1) (balanced digits hold
+// 0.996 times that), and its scale is 2^(8 D) / s (NaN for a row with an
+// infinity or NaN, whose digits are zero).  Digit i of the half hf (columns
+// 64 hf ..) of output tile t is fragment 2 D t + D hf + i, 16 bytes at lane
+// 16 g + c: byte 4 T + q is row 16 t + c, column 64 hf + 16 T + 4 g + q.
+template <int D>
+void pack_digits(const double* M, int nout, int precision, std::vector<unsigned char>* out) {
+  constexpr int W = kEncWidth;
+  constexpr uint64_t kOffset = 0x80808080808080ull >> (8 * (7 - D));
+  const size_t at = out->size();
+  out->resize(at + size_t(nout) * W * D);
+  unsigned char* frag = out->data() + at;
+  std::vector<double> scale(static_cast<size_t>(nout));
   for (int o = 0; o < nout; ++o) {
     double top = 0.0;
     bool finite = true;
@@ -161,21 +172,22 @@ void pack_digits(const double* M, int nout, std::vector<double>* out) {
     int E = 0;
     const double lead = finite && top > 0.0 ? std::frexp(top, &E) : 1.0;
     const double down1 = std::ldexp(1.0, -E / 2), down2 = std::ldexp(1.0, -(E - E / 2));
-    const double s = 0.99 * 0x1p55 / lead;
-    (*out)[at + frag_doubles + size_t(o)] = finite ? std::ldexp(0x1p56 / s, E) : std::nan("");
+    const double s = 0.99 * std::ldexp(1.0, 8 * D - 1) / lead;
+    scale[size_t(o)] = finite ? std::ldexp(std::ldexp(1.0, 8 * D) / s, E) : std::nan("");
     for (int hf = 0; hf < 2; ++hf)
       for (int g = 0; g < 4; ++g) {
         unsigned char lane[D][16];
         for (int b = 0; b < 16; ++b) {
           const double v = finite ? M[size_t(o) * W + 64 * hf + 16 * (b / 4) + 4 * g + b % 4] * down1 * down2 * s : 0.0;
           // an offset of 128 in every digit turns them into plain bytes
-          const uint64_t x = (uint64_t(int64_t(v + (v < 0 ? -0.5 : 0.5))) + 0x80808080808080ull) ^ 0x80808080808080ull;
+          const uint64_t x = (uint64_t(int64_t(v + (v < 0 ? -0.5 : 0.5))) + kOffset) ^ kOffset;
           for (int i = 0; i < D; ++i) lane[i][b] = (unsigned char)(x >> (8 * (D - 1 - i)));
         }
         unsigned char* p = frag + (size_t(o / 16) * 2 * D + size_t(hf) * D) * 1024 + (16 * g + o % 16) * 16;
         for (int i = 0; i < D; ++i) std::memcpy(p + size_t(i) * 1024, lane[i], 16);
       }
   }
+  append_values(scale.data(), scale.size(), precision, out);
 }
 
 // Copy host values to the device in the kernel's arithmetic type.
@@ -485,30 +497,23 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   ctx->head_stride = head_table_elems(nin, hp->reg_hidden);
   ctx->elem_bytes = hp->precision == 64 ? sizeof(double) : sizeof(float);
   const int prec = hp->precision;
-  // encoder fragments per 16-byte load: hidden layers (8 output tiles) and
-  // output layer (k/16 tiles); the head keeps one fragment per load
-  const int vw_hid = int(16 / ctx->elem_bytes);
-  const int vw_out = std::min(vw_hid, k / 16);
-
-  // encoder tables -> [w0 b0 | (fragments(W_t) b_t)... | fragments(W_out) b_out],
-  // in float64 digits and row scales in place of each matrix's fragments
-  std::vector<double> enc;
-  enc.reserve(ctx->enc_stride * ctx->n_enc);
+  // encoder tables -> [w0 b0 | (digits(W_t) row scales b_t)... | digits(W_out)
+  // row scales b_out]
+  std::vector<unsigned char> enc;
+  enc.reserve(ctx->enc_stride * ctx->n_enc * ctx->elem_bytes);
   const double* src = weights_host;
   const size_t W = kEncWidth;
   for (int t = 0; t < ctx->n_enc; ++t) {
     const double* p = src + size_t(t) * enc_blob_doubles(hp);
-    enc.insert(enc.end(), p, p + 2 * W);
+    append_values(p, 2 * W, prec, &enc);
     p += 2 * W;
-    for (int h = 1; h < hp->enc_hidden; ++h) {
-      if (prec == 64) pack_digits(p, kEncWidth, &enc);
-      else pack_fragments(p, kEncWidth, kEncWidth, prec, vw_hid, &enc);
-      enc.insert(enc.end(), p + W * W, p + W * W + W);
-      p += W * W + W;
+    for (int h = 1; h <= hp->enc_hidden; ++h) {
+      const int rows = h < hp->enc_hidden ? kEncWidth : k;
+      if (prec == 64) pack_digits<weight_digits(64)>(p, rows, prec, &enc);
+      else pack_digits<weight_digits(32)>(p, rows, prec, &enc);
+      append_values(p + size_t(rows) * W, size_t(rows), prec, &enc);
+      p += size_t(rows) * W + size_t(rows);
     }
-    if (prec == 64) pack_digits(p, k, &enc);
-    else pack_fragments(p, k, kEncWidth, prec, vw_out, &enc);
-    enc.insert(enc.end(), p + size_t(k) * W, p + size_t(k) * W + k);
   }
   // head tables -> [frag(A0) | frag(A0^T) | c0 | (frag(A_t) frag(A_t^T) c_t)... | a_out c_out]
   std::vector<double> head;
@@ -517,13 +522,13 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   const int R = kHeadWidth;
   for (int t = 0; t < ctx->n_head; ++t) {
     const double* p = hsrc + size_t(t) * head_blob_doubles(hp);
-    pack_fragments(p, R, nin, prec, 1, &head);
-    pack_fragments(transpose(p, R, nin).data(), nin, R, prec, 1, &head);
+    pack_fragments(p, R, nin, prec, &head);
+    pack_fragments(transpose(p, R, nin).data(), nin, R, prec, &head);
     head.insert(head.end(), p + size_t(R) * nin, p + size_t(R) * nin + R);
     p += size_t(R) * nin + R;
     for (int h = 1; h < hp->reg_hidden; ++h) {
-      pack_fragments(p, R, R, prec, 1, &head);
-      pack_fragments(transpose(p, R, R).data(), R, R, prec, 1, &head);
+      pack_fragments(p, R, R, prec, &head);
+      pack_fragments(transpose(p, R, R).data(), R, R, prec, &head);
       head.insert(head.end(), p + R * R, p + R * R + R);
       p += R * R + R;
     }
@@ -535,7 +540,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   std::vector<double> qc;
   std::string err;
   if (!build_angular_table(hp->lmax, hp->angular, qrows, qcols, &qc, ctx->lrow, &err) ||
-      enc.size() != ctx->enc_stride * ctx->n_enc ||
+      enc.size() != ctx->enc_stride * ctx->n_enc * ctx->elem_bytes ||
       head.size() != ctx->head_stride * ctx->n_head) {
     delete ctx;
     return create_fail(MLIP_E_ARG, err.empty() ? "weight repacking size mismatch" : "angular table: " + err);
@@ -543,7 +548,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   size_t cap = 0, cap2 = 0, cap3 = 0, cap4 = 0, cap5 = 0, cap6 = 0, cap7 = 0, cap8 = 0;
   mlip_status st = MLIP_OK;
   const size_t eb = ctx->elem_bytes;
-  if ((st = ensure(ctx, &ctx->d_enc, &cap, enc.size() * eb, "encoder")) != MLIP_OK ||
+  if ((st = ensure(ctx, &ctx->d_enc, &cap, enc.size(), "encoder")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_head, &cap2, head.size() * eb, "head")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_qc, &cap3, qc.size() * eb, "tables")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_totals, &cap4, size_t(16), "totals")) != MLIP_OK ||
@@ -555,7 +560,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     mlip_destroy(ctx);
     return create_fail(st, msg);
   }
-  if (upload(ctx->d_enc, enc.data(), enc.size(), eb) != hipSuccess ||
+  if (hipMemcpy(ctx->d_enc, enc.data(), enc.size(), hipMemcpyHostToDevice) != hipSuccess ||
       upload(ctx->d_head, head.data(), head.size(), eb) != hipSuccess ||
       upload(ctx->d_qc, qc.data(), qc.size(), eb) != hipSuccess) {
     (void)hipGetLastError();

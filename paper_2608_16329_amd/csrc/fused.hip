@@ -41,8 +41,10 @@
 // The result layout differs: register q of lane holds D[drow(q, g)][c] with
 // drow = 4q + g for float64 and 4g + q for float32.  A D-tile X can feed a
 // later product as B (contracting over its rows; k-step q covers rows
-// drow(q, 0..3)) or as A (X^T, same contraction); the host packs weight
-// fragments with the same row map.
+// drow(q, 0..3)) or as A (X^T, same contraction); the host packs the head's
+// weight fragments with the same row map.  The 8-bit integer 16x16x64 product
+// of the encoder takes 16 bytes per lane (A[c][16g ..], B[16g ..][c]) and
+// returns row 4g + q in both precisions.
 //
 // The file is compiled in three parts (MLIP_FUSED_PART), whose instantiations
 // build in parallel: 1 float64 to l_max 3 and the entry, 2 float64 with l_max
@@ -140,6 +142,17 @@ __device__ __forceinline__ float sigmoid(float z) {
   const float e = __builtin_amdgcn_exp2f(-z * kLog2e);
   return __builtin_amdgcn_rcpf(1.0f + e);
 }
+
+struct NoConst {};
+__device__ __forceinline__ float sigmoid(float z, const NoConst&) { return sigmoid(z); }
+template <typename R>
+struct SigmoidOf {
+  typedef SigmoidConst Const;
+};
+template <>
+struct SigmoidOf<float> {
+  typedef NoConst Const;
+};
 
 // Slope of the SiLU z s(z), s (1 + z (1 - s)), as two fused multiply-adds:
 // t = z - s z = z (1 - s), then s + s t.
@@ -370,13 +383,6 @@ __device__ __forceinline__ PairPos load_pair_pos(const FusedArgs& A, const Smem<
   return p;
 }
 
-// Weight-fragment streaming of the encoder products: fragments of VW
-// consecutive output tiles per 16-byte load, through register rings issued
-// kRing - 1 (hidden layers) or kRingO - 1 (output layer) k-steps ahead of the
-// MFMAs that consume them.  An output-layer k-step is only 2 KT products, so
-// its ring runs further ahead.  The float32 kernel runs two wavefronts per
-// SIMD, which cover each other's load latency; there shallower rings leave
-// more registers and measured faster (ring depths 2 and 4 against 3 and 8).
 // Fragment array at a wave-uniform address, read through a buffer descriptor:
 // the descriptor and each group's offset are scalar and the lane offset is
 // one fixed vector register, so walking the array costs no vector address
@@ -399,47 +405,16 @@ struct FragStream {
   }
 };
 
-// Bias vector of a hidden layer at a wave-uniform address, read through a
-// buffer descriptor in the accumulator row order: element (To, q) of lane
-// (g, c) is row 16 To + drow(q, g); the lane part of that offset is one
-// fixed vector register, the rest a scalar offset.  With bytes = 0 every
-// read returns zero without touching memory.
+// Per-row values of a weight matrix at a wave-uniform address: the four rows
+// 16 To + 4 g + q of a lane.
 template <typename R>
-struct BiasStream {
-  __amdgpu_buffer_rsrc_t rs;
-  int lo;
-  __device__ __forceinline__ BiasStream(const void* base, int bytes, int g)
-      : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRawBufferConfig)),
-        lo((sizeof(R) == 8 ? g : 4 * g) * int(sizeof(R))) {}
-  __device__ __forceinline__ R operator()(int To, int q) const {
-    const int so = (16 * To + (sizeof(R) == 8 ? 4 * q : q)) * int(sizeof(R));
-    if constexpr (sizeof(R) == 8) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, lo, so, 0));
-    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, lo, so, 0));
-  }
-};
-
-// Per-row values (float64) of a weight matrix at a wave-uniform address: the
-// four rows 16 To + 4 g + q of a lane.
 struct RowStream {
-  const double* p;
-  __device__ __forceinline__ RowStream(const double* base, int g) : p(base + 4 * g) {}
-  __device__ __forceinline__ void load(int To, double (&v)[4]) const {
+  const R* p;
+  __device__ __forceinline__ RowStream(const R* base, int g) : p(base + 4 * g) {}
+  __device__ __forceinline__ void load(int To, R (&v)[4]) const {
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = p[16 * To + q];
   }
-};
-
-template <int K, typename R>
-struct Stream {
-  static constexpr int KT = K / 16;
-  static constexpr int VW = 16 / int(sizeof(R));  // fragments per load
-  static constexpr int NH = 8 / VW;               // loads per hidden-layer k-step
-  static constexpr int VO = KT < VW ? KT : VW;    // fragments per output-layer load
-  static constexpr int NO = KT / VO;              // loads per output-layer k-step
-  static constexpr int kRing = sizeof(R) == 8 ? 3 : 2;
-  static constexpr int kRingO = sizeof(R) == 8 ? 8 : 4;
-  typedef R vh_t __attribute__((ext_vector_type(VW)));
-  typedef R vo_t __attribute__((ext_vector_type(VO)));
 };
 
 // Row of the encoder's hidden activations held in register q of a lane of
@@ -447,25 +422,45 @@ struct Stream {
 // contracts the columns of m.
 __device__ __forceinline__ int hrow(int q, int g) { return 4 * g + q; }
 
-// ---- float64 products on the 8-bit integer matrix pipe ----------------------
+// ---- products on the 8-bit integer matrix pipe ------------------------------
 // A float64 MFMA runs at the rate of float64 FMAs and holds the vector pipe
-// for its whole duration; 8-bit integer MFMAs run 64 times as fast and leave
-// the vector pipe free.  The encoder's float64 products are therefore split
-// error-free (Ozaki's scheme): with a scale per weight row and per activation
-// column, both operands become 56-bit integers written as seven balanced
-// base-256 digits, X = sum_i d_i 256^(6-i), d_i in [-128, 127], and
-//   sum_k X_k Y_k = sum_i sum_j 256^(12-i-j) sum_k d_i[k] e_j[k],
+// for its whole duration; 8-bit integer MFMAs run 64 times as fast (32 times a
+// float32 MFMA) and leave the vector pipe free.  The encoder's products are
+// therefore split error-free (Ozaki's scheme): with a scale per weight row and
+// per activation column, both operands become integers of balanced base-256
+// digits, X = sum_i d_i 256^(D-1-i), d_i in [-128, 127], and
+//   sum_k X_k Y_k = sum_i sum_j 256^(D+D'-2-i-j) sum_k d_i[k] e_j[k],
 // whose inner sums are exact in 32 bits (128 products of at most 2^14, at
-// most seven of them per i + j: below 2^24).  The 28 digit products with
-// i + j <= 6 are formed; what is left out is below 2^-53 of the result's size
-// (measured against a float64 reference the outputs are as close as with
-// float64 MFMAs: 7.7e-16, 4.6e-15 and 4.0e-15 of E, F and w at 1,048,576 atoms,
-// 8.1e-16, 4.6e-15 and 4.0e-15 before).  An encoder call of 16 pairs (two
-// hidden layers) takes 59 thousand cycles at 2.1 GHz, 28 us, instead of 91
-// thousand at 2.34 GHz, 39 us; the kernel 198.6 ms instead of 251.0 ms at
-// 1,048,576 atoms of six species.  What bounds it now is vector issue: about
-// 76 vector instructions per activation and tangent beside 28 MFMAs.
-constexpr int kDigits = 7;
+// most seven of them per i + j: below 2^24).
+//
+// float64: seven digits (56 bits), the 28 digit products with i + j <= 6; what
+// is left out is below 2^-53 of the result's size.  Measured against a float64
+// reference the outputs are as close as with float64 MFMAs: 7.7e-16, 4.6e-15
+// and 4.0e-15 of E, F and w at 1,048,576 atoms, 8.1e-16, 4.6e-15 and 4.0e-15
+// before.  An encoder call of 16 pairs (two hidden layers) takes 59 thousand
+// cycles at 2.1 GHz, 28 us, instead of 91 thousand at 2.34 GHz, 39 us; the
+// kernel 198.6 ms instead of 251.0 ms at 1,048,576 atoms of six species.
+//
+// float32: weights of four digits, activations of three (24 bits), the nine
+// digit products with i + j <= 3 (with three digits both, and still more with
+// six products, the outputs were further from float64 than with float32
+// MFMAs): 3.42e-7, 1.51e-6 and 1.38e-6 of E, F and w at 1,048,576 atoms,
+// 3.45e-7, 1.58e-6 and 1.44e-6 with float32 MFMAs.  List and evaluation of
+// these atoms take 90 ms instead of 132.
+//
+// What bounds it is vector issue: about 76 (float64) and 40 (float32) vector
+// instructions per activation and tangent beside 28 and 9 MFMAs.
+template <typename R>
+struct Split;
+template <>
+struct Split<double> {
+  static constexpr int W = 7, D = 7, S = 7;  // digits of weights and activations, sums (i + j < S)
+};
+template <>
+struct Split<float> {
+  static constexpr int W = 4, D = 3, S = 4;
+};
+static_assert(Split<double>::W == weight_digits(64) && Split<float>::W == weight_digits(32), "packed digits");
 typedef int v4i __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
   return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
@@ -474,19 +469,24 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 // Activation columns in digits: s[i][hf] holds digit i of the rows
 // 64 hf + 16 t + 4 g + q of column c in byte 4 t + q, which is both the B
 // operand (rows as k) and the A operand (columns as rows) of a 16x16x64
-// product.  inv: value of one unit of 2^32 of the integers.
+// product.  inv: value of a unit of the top three digits.
+template <typename R>
 struct Digits {
-  v4i s[kDigits][2];
-  double inv;
+  v4i s[Split<R>::D][2];
+  R inv;
 };
 
 // Scale that takes a column's largest magnitude (over the lane's 32 values
 // and its column's four lanes) to just below 0.99 x 2^23: the closer to the
 // full range, the less the digit products that are left out weigh.  A column
 // with an infinity or NaN gets a NaN inverse, so everything formed from it is
-// NaN; one of zeros (or below 2^-974) gets scale and inverse zero.
-__device__ __forceinline__ double digit_scale(const double (&h)[8][4], Digits& d) {
-  // largest magnitude by the high words: as signed integers for positive
+// NaN; one of zeros (or below 2^-974, in float32 2^-100) gets scale and inverse
+// zero.
+__device__ __forceinline__ int top_bits(double x) { return __double2hiint(x); }
+__device__ __forceinline__ int top_bits(float x) { return __float_as_int(x); }
+template <typename R>
+__device__ __forceinline__ R digit_scale(const R (&h)[8][4], Digits<R>& d) {
+  // largest magnitude by the (high) words: as signed integers for positive
   // values, as unsigned for negative ones
   int mp = 0;
   unsigned mn = 0;
@@ -494,22 +494,32 @@ __device__ __forceinline__ double digit_scale(const double (&h)[8][4], Digits& d
   for (int T = 0; T < 8; ++T)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int hi = __double2hiint(h[T][q]);
+      const int hi = top_bits(h[T][q]);
       mp = max(mp, hi);
       mn = max(mn, unsigned(hi));
     }
   unsigned m = max(unsigned(mp), mn >> 31 ? mn & 0x7fffffffu : 0u);
   m = max(m, unsigned(__shfl_xor(int(m), 16, 64)));
   m = max(m, unsigned(__shfl_xor(int(m), 32, 64)));
-  const double top = __hiloint2double(int(m + 1), 0);  // above every magnitude of the column
-  constexpr double kRange = 0.99 * 8388608.0;          // seven balanced digits hold 0.996 x 2^23 x 2^32
-  const double y = __builtin_amdgcn_rcp(top);
-  double scale = kRange * fma(fma(-top, y, 1.0), y, y);
-  double inv = top * (1.0 / kRange);
-  inv = fma(fma(-scale, inv, 1.0), inv, inv);
-  if (m - 0x03100000u >= 0x7fd00000u - 0x03100000u) {
-    scale = 0.0;
-    inv = m >= 0x7fd00000u ? __hiloint2double(0x7ff80000, 0) : 0.0;
+  constexpr double kRange = 0.99 * 8388608.0;  // seven balanced digits hold 0.996 x 2^23 x 2^32
+  R scale, inv;
+  unsigned low, high;  // range of m whose scale and inverse are normal
+  if constexpr (sizeof(R) == 8) {
+    const double top = __hiloint2double(int(m + 1), 0);  // above every magnitude of the column
+    const double y = __builtin_amdgcn_rcp(top);
+    scale = kRange * fma(fma(-top, y, 1.0), y, y);
+    inv = top * (1.0 / kRange);
+    low = 0x03100000u, high = 0x7fd00000u;
+  } else {
+    const float top = __int_as_float(int(m));
+    scale = float(kRange) * __builtin_amdgcn_rcpf(top);
+    inv = top * float(1.0 / kRange);
+    low = 0x0d800000u, high = 0x7e800000u;
+  }
+  inv = fma(fma(-scale, inv, R(1)), inv, inv);
+  if (m - low >= high - low) {
+    scale = R(0);
+    inv = m >= high ? R(__builtin_nanf("")) : R(0);
   }
   d.inv = inv;
   return scale;
@@ -522,7 +532,7 @@ __device__ __forceinline__ double digit_scale(const double (&h)[8][4], Digits& d
 // (0x808080 in the upper 24 bits, 0x80808080 in the lower 32) makes the digits
 // the bytes of a non-negative integer, up to the offset itself, taken off by
 // flipping each byte's top bit.
-__device__ __forceinline__ void make_digits(const double (&h)[8][4], double scale, int hf, Digits& d) {
+__device__ __forceinline__ void make_digits(const double (&h)[8][4], double scale, int hf, Digits<double>& d) {
   constexpr double kShift = 6755399441055744.0;
   double upper = kShift + 8421504.0, lower = kShift + 2155905152.0, two32 = 4294967296.0;
   // opaque, or their copies for accumulating instructions would outnumber
@@ -546,37 +556,63 @@ __device__ __forceinline__ void make_digits(const double (&h)[8][4], double scal
     const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
     const unsigned p = __builtin_amdgcn_perm(lw[1], lw[0], 0x07030602u), q = __builtin_amdgcn_perm(lw[3], lw[2], 0x07030602u);
     const unsigned r = __builtin_amdgcn_perm(lw[1], lw[0], 0x05010400u), z = __builtin_amdgcn_perm(lw[3], lw[2], 0x05010400u);
-    const unsigned w[kDigits] = {
+    const unsigned w[7] = {
         __builtin_amdgcn_perm(f, e, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u),
         __builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(q, p, 0x07060302u),
         __builtin_amdgcn_perm(q, p, 0x05040100u), __builtin_amdgcn_perm(z, r, 0x07060302u),
         __builtin_amdgcn_perm(z, r, 0x05040100u)};
 #pragma unroll
-    for (int i = 0; i < kDigits; ++i) d.s[i][hf][t] = int(w[i] ^ 0x80808080u);
+    for (int i = 0; i < 7; ++i) d.s[i][hf][t] = int(w[i] ^ 0x80808080u);
   }
   // kept in accumulation registers: matrix operands only from here on
 #pragma unroll
-  for (int i = 0; i < kDigits; ++i) asm("" : "+a"(d.s[i][hf]));
+  for (int i = 0; i < 7; ++i) asm("" : "+a"(d.s[i][hf]));
 }
-__device__ __forceinline__ void make_digits(const double (&h)[8][4], Digits& d) {
-  const double scale = digit_scale(h, d);
+// float32: the three digits of the value rounded to an integer.
+__device__ __forceinline__ void make_digits(const float (&h)[8][4], float scale, int hf, Digits<float>& d) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    unsigned hw[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hw[q] = unsigned(int(__builtin_rintf(h[4 * hf + t][q] * scale))) + 0x808080u;
+    const unsigned a = __builtin_amdgcn_perm(hw[1], hw[0], 0x05010400u), b = __builtin_amdgcn_perm(hw[3], hw[2], 0x05010400u);
+    const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
+    d.s[0][hf][t] = int(__builtin_amdgcn_perm(f, e, 0x05040100u) ^ 0x80808080u);
+    d.s[1][hf][t] = int(__builtin_amdgcn_perm(b, a, 0x07060302u) ^ 0x80808080u);
+    d.s[2][hf][t] = int(__builtin_amdgcn_perm(b, a, 0x05040100u) ^ 0x80808080u);
+  }
+}
+template <typename R>
+__device__ __forceinline__ void make_digits(const R (&h)[8][4], Digits<R>& d) {
+  const R scale = digit_scale(h, d);
   make_digits(h, scale, 0, d);
   make_digits(h, scale, 1, d);
 }
 
-// Sum of the digit products, S[d] = sum over i + j = d, in units of 2^88:
-// 2^8 sum_d S[d] 2^(-8d), exact up to the last rounding (and to 2^-40 of a
-// unit of S[0]).  The pairs that are merged as integers stay below 2^31.
-__device__ __forceinline__ double digit_sum(const v4i (&S)[kDigits], int q) {
+// Sum of the digit products, S[d] = sum over i + j = d:
+// 2^8 sum_d S[d] 2^(-8d), exact up to the last rounding (float64: and to 2^-40
+// of a unit of S[0]; float32: up to the rounding of the two merged sums).  The
+// pairs that are merged as integers stay below 2^31.
+__device__ __forceinline__ double digit_sum(const v4i (&S)[7], int q) {
   const int a = (S[0][q] << 8) + S[1][q], b = (S[2][q] << 8) + S[3][q], e = S[5][q] + (S[6][q] >> 8);
   double t = fma(double(S[4][q]), 0x1p-8, double(b));
   t = fma(double(e), 0x1p-16, t);
   return fma(t, 0x1p-16, double(a));
 }
+__device__ __forceinline__ float digit_sum(const v4i (&S)[4], int q) {
+  const int a = (S[0][q] << 8) + S[1][q], b = (S[2][q] << 8) + S[3][q];
+  return fma(float(b), 0x1p-16f, float(a));
+}
 
-// Weight tile of an integer product: digit i of half hf is fragment 7 hf + i
+// Weight tile of an integer product: digit i of half hf is fragment W hf + i
 // (64 lanes of 16 bytes).
-constexpr int kTileFrags = 2 * kDigits;
+template <typename R>
+constexpr int kTileFrags = 2 * Split<R>::W;
+// Values of R that the fragments of n tiles take in a table.
+template <typename R>
+constexpr int frag_values(int n) {
+  return n * kTileFrags<R> * 1024 / int(sizeof(R));
+}
 
 // Minimum-image vector r_ij of the pair in column c of chunk ch (Eq. 1), in
 // float64; (1, 0, 0) and atom -1 for the padding columns of a partial chunk.
@@ -604,262 +640,36 @@ __device__ __forceinline__ const R* chunk_table(const FusedArgs& A, const Smem<K
   return static_cast<const R*>(A.enc) + (long long)tau * A.enc_stride;
 }
 
-// What the hidden layers leave for the output layer: float32 the activations
-// and their tangents (rows 16T + 4g + i of column c), float64 their digits.
+// What the hidden layers leave for the output layer.
 template <typename R>
-struct Hidden;
-template <>
-struct Hidden<float> {
-  float h[8][4], dh[8][4];
-};
-template <>
-struct Hidden<double> {
-  Digits h, dh;
+struct Hidden {
+  Digits<R> h, dh;
 };
 
-// Encoder forward and tangent (Eq. 2 and its derivative in r) up to the last
-// hidden layer for the 16 pairs of a chunk: the first layer (scalar input)
-// from the LDS copy of (w0, b0), then the residual hidden layers Z = W H as
-// 8 x 32 MFMA steps whose forward and tangent columns share each weight
-// fragment.  On return h[T][i], dh[T][i] hold rows 16T + 4g + i of
-// column c; the result is the output-layer section of the table.  Without
-// kTan only the forward runs (dh is left untouched): the moment needs the
-// encoder output alone, so a pass 1 that keeps no workspace skips the
-// tangent's half of the products.
-template <int K, int TM, int NW, int DR, int NM, bool kTan = true>
-__device__ __forceinline__ const float* encoder_hidden(const FusedArgs& A, const Smem<K, TM, float, NW, DR, NM>& S,
-                                                       int sj, float r, const float* __restrict__ tab,
-                                                       Hidden<float>& out) {
-  typedef float R;
-  float(&h)[8][4] = out.h;
-  float(&dh)[8][4] = out.dh;
-  typedef Stream<K, R> St;
-  typedef typename St::vh_t vh_t;
-  constexpr int NH = St::NH, VW = St::VW, kRing = St::kRing;
-  const int lane = phase_tid() & 63, g = lane >> 4;
-  constexpr int kLayerBytes = int(kEncWidth * kEncWidth * sizeof(R));
-  constexpr int kBiasBytes = int(kEncWidth * sizeof(R));
-  const int nh = A.enc_hidden;
-  // The first hidden layer's leading weight fragments are requested before
-  // the elementwise first layer, whose activation work covers their
-  // latency; each hidden layer requests the next one's in its last k-steps,
-  // so they arrive during its own activation phase.  Past the last hidden
-  // layer that descriptor has size 0 and reads zeros.  At k = 64 the wider
-  // output tiles leave no registers for fragments held across an activation
-  // phase (it measured slower): there each layer fills its ring at its start.
-  constexpr bool kCross = K <= 32;
-  const R* __restrict__ layer = tab + 2 * kEncWidth;
-  vh_t wb[kRing][NH];
-  v4<R> acc[8], dacc[8];
-  if constexpr (kCross) {
-    const FragStream<vh_t> frag(layer, nh > 1 ? kLayerBytes : 0);
-#pragma unroll
-    for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-      for (int u = 0; u < NH; ++u) wb[p][u] = frag[p * NH + u];
-  }
-#pragma unroll
-  for (int T = 0; T < 8; ++T)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int in = 16 * T + hrow(i, g);
-      const R w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
-      const R s = sigmoid(z);
-      h[T][i] = z * s;
-      if constexpr (kTan) dh[T][i] = silu_slope(z, s) * w0;
-    }
-  for (int t = 1; t < nh; ++t) {
-    const FragStream<vh_t> frag(layer, kLayerBytes);
-    const R* __restrict__ next = layer + kEncWidth * kEncWidth + kEncWidth;
-    const bool more = t + 1 < nh;
-    const FragStream<vh_t> nfrag(next, more ? kLayerBytes : 0);
-    if constexpr (!kCross) {
-#pragma unroll
-      for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-        for (int u = 0; u < NH; ++u) wb[p][u] = frag[p * NH + u];
-    }
-    // the tangent has no bias
-    {
-      const BiasStream<R> bias(layer + kEncWidth * kEncWidth, kBiasBytes, g);
-#pragma unroll
-      for (int To = 0; To < 8; ++To) acc[To] = v4<R>{bias(To, 0), bias(To, 1), bias(To, 2), bias(To, 3)};
-    }
-#pragma unroll
-    for (int To = 0; To < 8; ++To) dacc[To] = v4<R>{0, 0, 0, 0};
-#pragma unroll
-    for (int ks = 0; ks < 32; ++ks) {
-      const int kn = ks + kRing - 1;
-      if (kCross || kn < 32) {
-#pragma unroll
-        for (int u = 0; u < NH; ++u) wb[kn % kRing][u] = kn < 32 ? frag[kn * NH + u] : nfrag[(kn - 32) * NH + u];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      const int T = ks >> 2, i = ks & 3;
-#pragma unroll
-      for (int To = 0; To < 8; ++To) {
-        const R wv = wb[ks % kRing][To / VW][To % VW];
-        acc[To] = mfma(wv, h[T][i], acc[To]);
-        if constexpr (kTan) dacc[To] = mfma(wv, dh[T][i], dacc[To]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // the next layer's k-step p sits in slot (32 + p) mod kRing; it starts
-    // from slot p (a no-op when kRing divides 32)
-    if constexpr (kCross && 32 % kRing != 0) {
-      vh_t nx[kRing - 1][NH];
-#pragma unroll
-      for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-        for (int u = 0; u < NH; ++u) nx[p][u] = wb[(32 + p) % kRing][u];
-#pragma unroll
-      for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-        for (int u = 0; u < NH; ++u) wb[p][u] = nx[p][u];
-    }
-#pragma unroll
-    for (int To = 0; To < 8; ++To) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const R z = acc[To][q];
-        const R s = sigmoid(z);
-        h[To][q] += z * s;
-        if constexpr (kTan) dh[To][q] = fma(silu_slope(z, s), dacc[To][q], dh[To][q]);
-      }
-    }
-    layer = next;
-  }
-  return layer;
-}
-
-// Encoder output layer with pairs as rows: mo[Tc] register q holds
-// m[pair drow(q, g)][16Tc + c] (dmo the same for the tangent, computed only
-// with kTan).  Even and odd k-steps accumulate separately so 4 KT independent
-// MFMA chains are in flight; the bias is added at the end so the first
-// products do not wait for its load.
-template <int K, bool kTan = true>
-__device__ __forceinline__ void encoder_out_rows(const float* __restrict__ layer, const Hidden<float>& in,
-                                                 v4f (&mo)[K / 16], v4f (&dmo)[K / 16]) {
-  typedef float R;
-  const float(&h)[8][4] = in.h;
-  const float(&dh)[8][4] = in.dh;
-  typedef Stream<K, R> St;
-  typedef typename St::vo_t vo_t;
-  constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
-  const int lane = phase_tid() & 63, c = lane & 15;
-  const R* __restrict__ bout = layer + K * kEncWidth;
-  v4<R> mo2[2][KT], dmo2[2][KT];
-  R b[KT];
-#pragma unroll
-  for (int Tc = 0; Tc < KT; ++Tc) {
-    b[Tc] = bout[16 * Tc + c];
-    mo2[0][Tc] = mo2[1][Tc] = dmo2[0][Tc] = dmo2[1][Tc] = v4<R>{0, 0, 0, 0};
-  }
-  const FragStream<vo_t> frag(layer, int(K * kEncWidth * sizeof(R)));
-  vo_t wo[kRing][NO];
-#pragma unroll
-  for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-    for (int u = 0; u < NO; ++u) wo[p][u] = frag[p * NO + u];
-#pragma unroll
-  for (int ks = 0; ks < 32; ++ks) {
-    if (ks + kRing - 1 < 32) {
-#pragma unroll
-      for (int u = 0; u < NO; ++u) wo[(ks + kRing - 1) % kRing][u] = frag[(ks + kRing - 1) * NO + u];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const int T = ks >> 2, i = ks & 3;
-#pragma unroll
-    for (int Tc = 0; Tc < KT; ++Tc) {
-      const R wv = wo[ks % kRing][Tc / VO][Tc % VO];
-      mo2[ks & 1][Tc] = mfma(h[T][i], wv, mo2[ks & 1][Tc]);
-      if constexpr (kTan) dmo2[ks & 1][Tc] = mfma(dh[T][i], wv, dmo2[ks & 1][Tc]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int Tc = 0; Tc < KT; ++Tc) {
-    mo[Tc] = mo2[0][Tc] + mo2[1][Tc] + v4<R>{b[Tc], b[Tc], b[Tc], b[Tc]};
-    if constexpr (kTan) dmo[Tc] = dmo2[0][Tc] + dmo2[1][Tc];
-  }
-}
-
-// Encoder output layer with pairs as columns (the same fragments serve as
-// the A operand): register q of lane (g, c) for output tile Tc holds
-// m[pair c][16Tc + drow(q, g)], which is exactly the B operand of pass 2's
-// W m product.
-template <int K>
-__device__ __forceinline__ void encoder_out_cols(const float* __restrict__ layer, const Hidden<float>& in,
-                                                 float (&mB)[K / 16][4], float (&dmB)[K / 16][4]) {
-  typedef float R;
-  const float(&h)[8][4] = in.h;
-  const float(&dh)[8][4] = in.dh;
-  typedef Stream<K, R> St;
-  typedef typename St::vo_t vo_t;
-  constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
-  const int lane = phase_tid() & 63, g = lane >> 4;
-  const R* __restrict__ bout = layer + K * kEncWidth;
-  v4<R> acc[KT], dacc[KT];
-#pragma unroll
-  for (int Tc = 0; Tc < KT; ++Tc) {
-    acc[Tc] = v4<R>{bout[16 * Tc + drow<R>(0, g)], bout[16 * Tc + drow<R>(1, g)], bout[16 * Tc + drow<R>(2, g)],
-                    bout[16 * Tc + drow<R>(3, g)]};
-    dacc[Tc] = v4<R>{0, 0, 0, 0};
-  }
-  const FragStream<vo_t> frag(layer, int(K * kEncWidth * sizeof(R)));
-  vo_t wo[kRing][NO];
-#pragma unroll
-  for (int p = 0; p < kRing - 1; ++p)
-#pragma unroll
-    for (int u = 0; u < NO; ++u) wo[p][u] = frag[p * NO + u];
-#pragma unroll
-  for (int ks = 0; ks < 32; ++ks) {
-    if (ks + kRing - 1 < 32) {
-#pragma unroll
-      for (int u = 0; u < NO; ++u) wo[(ks + kRing - 1) % kRing][u] = frag[(ks + kRing - 1) * NO + u];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const int T = ks >> 2, i = ks & 3;
-#pragma unroll
-    for (int Tc = 0; Tc < KT; ++Tc) {
-      const R wv = wo[ks % kRing][Tc / VO][Tc % VO];
-      acc[Tc] = mfma(wv, h[T][i], acc[Tc]);
-      dacc[Tc] = mfma(wv, dh[T][i], dacc[Tc]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int Tc = 0; Tc < KT; ++Tc)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      mB[Tc][q] = acc[Tc][q];
-      dmB[Tc][q] = dacc[Tc][q];
-    }
-}
-
-// Products of half a 16-row weight tile (columns 64 hf .., fragments w[7 hf ..])
-// with the digits x of 16 columns: 28 MFMAs.  With kNext each fragment's
+// Products of half a 16-row weight tile (columns 64 hf .., fragments w[W hf ..])
+// with the digits x of 16 columns: 28 MFMAs in float64, 9 in float32.  With kNext each fragment's
 // registers take the fragment at next + f of the stream after its last use,
 // half a tile of products before that one is needed.  kRows: the activation
 // columns are the rows of the result.
-template <bool kRows, bool kNext>
-__device__ __forceinline__ void half_products(v4i (&w)[kTileFrags], const Digits& x, v4i (&S)[kDigits], int hf,
+template <bool kRows, bool kNext, typename R>
+__device__ __forceinline__ void half_products(v4i (&w)[kTileFrags<R>], const Digits<R>& x, v4i (&S)[Split<R>::S], int hf,
                                               const FragStream<v4i>& frag, int next) {
+  constexpr int W = Split<R>::W, D = Split<R>::D;
   if (hf == 0) {
 #pragma unroll
-    for (int i = 0; i < kDigits; ++i) S[i] = v4i{0, 0, 0, 0};
+    for (int i = 0; i < Split<R>::S; ++i) S[i] = v4i{0, 0, 0, 0};
   }
 #pragma unroll
-  for (int i = 0; i < kDigits; ++i) {
-    const int f = hf * kDigits + i;
+  for (int i = 0; i < W; ++i) {
+    const int f = hf * W + i;
 #pragma unroll
-    for (int j = 0; i + j < kDigits; ++j)
+    for (int j = 0; j < D && i + j < Split<R>::S; ++j)
       S[i + j] = kRows ? mfma_i8(x.s[j][hf], w[f], S[i + j]) : mfma_i8(w[f], x.s[j][hf], S[i + j]);
     if constexpr (kNext) w[f] = frag[next + f];
   }
 }
-template <bool kRows, bool kNext>
-__device__ __forceinline__ void tile_products(v4i (&w)[kTileFrags], const Digits& x, v4i (&S)[kDigits],
+template <bool kRows, bool kNext, typename R>
+__device__ __forceinline__ void tile_products(v4i (&w)[kTileFrags<R>], const Digits<R>& x, v4i (&S)[Split<R>::S],
                                               const FragStream<v4i>& frag, int next) {
   half_products<kRows, kNext>(w, x, S, 0, frag, next);
   half_products<kRows, kNext>(w, x, S, 1, frag, next);
@@ -873,12 +683,12 @@ __device__ __forceinline__ void park(double& x) { asm("" : "+a"(x)); }
 // load after its last use.  A 16x16x64 integer MFMA occupies the matrix pipe
 // for 16 cycles and issue for about 9, a vector instruction issue for 4 to 5
 // (measured on one wavefront), so two vector instructions fit beside each.
-template <int kValu, bool kLoads>
+template <typename R, int kValu, bool kLoads>
 __device__ __forceinline__ void interleave() {
 #pragma unroll
-  for (int i = 0; i < kDigits; ++i) {
+  for (int i = 0; i < Split<R>::W; ++i) {
 #pragma unroll
-    for (int j = 0; i + j < kDigits; ++j) {
+    for (int j = 0; j < Split<R>::D && i + j < Split<R>::S; ++j) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
     }
@@ -887,62 +697,71 @@ __device__ __forceinline__ void interleave() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// float64: each layer's products on digits (above), one 16-row tile at a
+// Encoder forward and tangent (Eq. 2 and its derivative in r) up to the last
+// hidden layer for the 16 pairs of a chunk: the first layer (scalar input)
+// from the LDS copy of (w0, b0), then the residual hidden layers Z = W H.
+// Without kTan only the forward runs: the moment needs the encoder output
+// alone, so a pass 1 that keeps no workspace skips the tangent's half.  The
+// result is the output-layer section of the table.
+//
+// Each layer's products are formed on digits (above), one 16-row tile at a
 // time: first the activations' products, then the tangents'.  The vector work
 // that turns a tile's sums into new activations is spread over the products
 // that follow, about two instructions per MFMA.
-template <int K, int TM, int NW, int DR, int NM, bool kTan = true>
-__device__ __forceinline__ const double* encoder_hidden(const FusedArgs& A, const Smem<K, TM, double, NW, DR, NM>& S,
-                                                        int sj, double r, const double* __restrict__ tab,
-                                                        Hidden<double>& out) {
+template <int K, int TM, typename R, int NW, int DR, int NM, bool kTan = true>
+__device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int sj, R r,
+                                                   const R* __restrict__ tab, Hidden<R>& out) {
   const int lane = phase_tid() & 63, g = lane >> 4;
-  constexpr int kFragBytes = 8 * kTileFrags * 1024;
+  constexpr int kFrags = frag_values<R>(8);
+  // float32 runs two wavefronts per SIMD, which fill each other's gaps; there
+  // the compiler's own order measured 2% faster
+  constexpr bool kOrder = sizeof(R) == 8;
   const int nh = A.enc_hidden;
-  const double* __restrict__ layer = tab + 2 * kEncWidth;
-  const SigmoidConst kc;
-  double h[8][4], dh[8][4];
+  const R* __restrict__ layer = tab + 2 * kEncWidth;
+  const typename SigmoidOf<R>::Const kc;
+  R h[8][4], dh[8][4];
 #pragma unroll
   for (int T = 0; T < 8; ++T)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int in = 16 * T + hrow(i, g);
-      const double w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
-      const double s = sigmoid(z, kc);
+      const R w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
+      const R s = sigmoid(z, kc);
       h[T][i] = z * s;
       if constexpr (kTan) {
         dh[T][i] = silu_slope(z, s) * w0;
       }
     }
   for (int t = 1; t < nh; ++t) {
-    const FragStream<v4i> frag(layer, kFragBytes);
-    const double* __restrict__ rows = layer + kFragBytes / 8;  // row scales, then biases
-    const RowStream scale(rows, g), bias(rows + kEncWidth, g);
-    v4i w[kTileFrags];
+    const FragStream<v4i> frag(layer, int(kFrags * sizeof(R)));
+    const R* __restrict__ rows = layer + kFrags;  // row scales, then biases
+    const RowStream<R> scale(rows, g), bias(rows + kEncWidth, g);
+    v4i w[kTileFrags<R>];
 #pragma unroll
-    for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
-    const double dsc = digit_scale(h, out.h);
-    double dsct = 0.0;
+    for (int f = 0; f < kTileFrags<R>; ++f) w[f] = frag[f];
+    const R dsc = digit_scale(h, out.h);
+    R dsct = 0;
     if constexpr (kTan) dsct = digit_scale(dh, out.dh);
     make_digits(h, dsc, 0, out.h);
-    v4i sf[kDigits], st[kDigits];
-    double sc[4], bi[4], z[4], slope[4];
+    v4i sf[Split<R>::S], st[Split<R>::S];
+    R sc[4], bi[4], z[4], slope[4];
     auto act = [&](int T, int q) {
-      const double s = sigmoid(z[q], kc);
+      const R s = sigmoid(z[q], kc);
       h[T][q] = fma(z[q], s, h[T][q]);
       if constexpr (kTan) slope[q] *= silu_slope(z[q], s);
     };
     auto sum = [&](int q) {
-      const double rs = sc[q];
+      const R rs = sc[q];
       z[q] = fma(digit_sum(sf, q) * rs, out.h.inv, bi[q]);
       if constexpr (kTan) slope[q] = rs * out.dh.inv;
     };
     auto tan_sum = [&](int T, int q) {
       dh[T][q] = fma(slope[q], digit_sum(st, q), dh[T][q]);
     };
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kOrder) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int To = 0; To <= 8; ++To) {
-      const int next = (To + 1) * kTileFrags;
+      const int next = (To + 1) * kTileFrags<R>;
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         if (To < 8 && hf == 1) {
@@ -960,11 +779,11 @@ __device__ __forceinline__ const double* encoder_hidden(const FusedArgs& A, cons
           if (hf == 0) make_digits(h, dsc, 1, out.h);
           else if constexpr (kTan) make_digits(dh, dsct, 0, out.dh);
         }
-        if (To < 8) {
-          if (To == 0) interleave<5, !kTan>();
-          else interleave<2, !kTan>();
+        if constexpr (kOrder) {
+          if (To == 0) interleave<R, 5, !kTan>();
+          else if (To < 8) interleave<R, 2, !kTan>();
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
       if (To == 8) continue;
       if constexpr (kTan) {
@@ -979,9 +798,11 @@ __device__ __forceinline__ const double* encoder_hidden(const FusedArgs& A, cons
             act(To, 0);
             act(To, 1);
           }
-          if (To == 0 && hf == 0) interleave<7, true>();
-          else interleave<2, true>();
-          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (kOrder) {
+            if (To == 0 && hf == 0) interleave<R, 7, true>();
+            else interleave<R, 2, true>();
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       } else {
 #pragma unroll
@@ -997,20 +818,20 @@ __device__ __forceinline__ const double* encoder_hidden(const FusedArgs& A, cons
   return layer;
 }
 
-// float64 output layer with pairs as rows: mo[Tc] register q holds
+// Encoder output layer with pairs as rows: mo[Tc] register q holds
 // m[pair 4g + q][16Tc + c] (dmo the same for the tangent).
-template <int K, bool kTan = true>
-__device__ __forceinline__ void encoder_out_rows(const double* __restrict__ layer, const Hidden<double>& in,
-                                                 v4d (&mo)[K / 16], v4d (&dmo)[K / 16]) {
+template <int K, typename R, bool kTan = true>
+__device__ __forceinline__ void encoder_out_rows(const R* __restrict__ layer, const Hidden<R>& in, v4<R> (&mo)[K / 16],
+                                                 v4<R> (&dmo)[K / 16]) {
   constexpr int KT = K / 16;
-  constexpr int kFragBytes = KT * kTileFrags * 1024;
+  constexpr int kFrags = frag_values<R>(KT);
   const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
-  const FragStream<v4i> frag(layer, kFragBytes);
-  const double* __restrict__ cols = layer + kFragBytes / 8;
-  v4i w[kTileFrags], sf[kDigits], st[kDigits];
+  const FragStream<v4i> frag(layer, int(kFrags * sizeof(R)));
+  const R* __restrict__ cols = layer + kFrags;
+  v4i w[kTileFrags<R>], sf[Split<R>::S], st[Split<R>::S];
 #pragma unroll
-  for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
-  double inv[4], dinv[4];
+  for (int f = 0; f < kTileFrags<R>; ++f) w[f] = frag[f];
+  R inv[4], dinv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     inv[q] = __shfl(in.h.inv, hrow(q, g), 64);
@@ -1018,9 +839,9 @@ __device__ __forceinline__ void encoder_out_rows(const double* __restrict__ laye
   }
 #pragma unroll
   for (int Tc = 0; Tc < KT; ++Tc) {
-    const double sc = cols[16 * Tc + c], b = cols[K + 16 * Tc + c];
-    tile_products<true, !kTan>(w, in.h, sf, frag, (Tc + 1) * kTileFrags);
-    if constexpr (kTan) tile_products<true, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags);
+    const R sc = cols[16 * Tc + c], b = cols[K + 16 * Tc + c];
+    tile_products<true, !kTan>(w, in.h, sf, frag, (Tc + 1) * kTileFrags<R>);
+    if constexpr (kTan) tile_products<true, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags<R>);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       mo[Tc][q] = fma(digit_sum(sf, q) * sc, inv[q], b);
@@ -1029,28 +850,28 @@ __device__ __forceinline__ void encoder_out_rows(const double* __restrict__ laye
   }
 }
 
-// float64 output layer with pairs as columns: register q of lane (g, c) for
+// Encoder output layer with pairs as columns: register q of lane (g, c) for
 // output tile Tc holds m[pair c][16Tc + 4g + q], the B operand of pass 2's
 // W m product.
-template <int K>
-__device__ __forceinline__ void encoder_out_cols(const double* __restrict__ layer, const Hidden<double>& in,
-                                                 double (&mB)[K / 16][4], double (&dmB)[K / 16][4]) {
+template <int K, typename R>
+__device__ __forceinline__ void encoder_out_cols(const R* __restrict__ layer, const Hidden<R>& in, R (&mB)[K / 16][4],
+                                                 R (&dmB)[K / 16][4]) {
   constexpr int KT = K / 16;
-  constexpr int kFragBytes = KT * kTileFrags * 1024;
+  constexpr int kFrags = frag_values<R>(KT);
   const int lane = phase_tid() & 63, g = lane >> 4;
-  const FragStream<v4i> frag(layer, kFragBytes);
-  const double* __restrict__ rows = layer + kFragBytes / 8;
-  const RowStream scale(rows, g), bias(rows + K, g);
-  v4i w[kTileFrags], sf[kDigits], st[kDigits];
+  const FragStream<v4i> frag(layer, int(kFrags * sizeof(R)));
+  const R* __restrict__ rows = layer + kFrags;
+  const RowStream<R> scale(rows, g), bias(rows + K, g);
+  v4i w[kTileFrags<R>], sf[Split<R>::S], st[Split<R>::S];
 #pragma unroll
-  for (int f = 0; f < kTileFrags; ++f) w[f] = frag[f];
+  for (int f = 0; f < kTileFrags<R>; ++f) w[f] = frag[f];
 #pragma unroll
   for (int Tc = 0; Tc < KT; ++Tc) {
-    double sc[4], b[4];
+    R sc[4], b[4];
     scale.load(Tc, sc);
     bias.load(Tc, b);
     tile_products<false, false>(w, in.h, sf, frag, 0);
-    tile_products<false, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags);
+    tile_products<false, true>(w, in.dh, st, frag, (Tc + 1) * kTileFrags<R>);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       mB[Tc][q] = fma(digit_sum(sf, q) * sc[q], in.h.inv, b[q]);
@@ -1093,10 +914,10 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
     }
     Hidden<R> hid;
     const R* __restrict__ layer =
-        encoder_hidden<K, TM, NW, DR, NM, kWs>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
+        encoder_hidden<K, TM, R, NW, DR, NM, kWs>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
     *next_ch = grab_chunk(&S.next_chunk[0]);
     if (*next_ch < nch) pp = load_pair_pos(A, S, *next_ch);
-    encoder_out_rows<K, kWs>(layer, hid, mo, dmo);
+    encoder_out_rows<K, R, kWs>(layer, hid, mo, dmo);
   }
   const int lane = phase_tid() & 63, g = lane >> 4, c = lane & 15;
   // chunk-wide values, in scalar registers
@@ -1218,8 +1039,8 @@ __device__ __forceinline__ void pass2_recompute(const FusedArgs& A, const Smem<K
   const R dx = R(dxd), dy = R(dyd), dz = R(dzd);
   const R r = vsqrt(dx * dx + dy * dy + dz * dz);
   Hidden<R> hid;
-  const R* __restrict__ layer = encoder_hidden<K, TM, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
-  encoder_out_cols<K>(layer, hid, in.mB, in.dmB);
+  const R* __restrict__ layer = encoder_hidden<K, TM, R, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
+  encoder_out_cols<K, R>(layer, hid, in.mB, in.dmB);
   in.pp = pp;
 }
 
@@ -1393,9 +1214,9 @@ __device__ void radial_chunk(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM
   cutoff(r, R(A.pi_rc), &fc, &dfc);
   if (!valid) fc = dfc = R(0);
   Hidden<R> hid;
-  const R* __restrict__ layer = encoder_hidden<K, TM, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
+  const R* __restrict__ layer = encoder_hidden<K, TM, R, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
   R mB[KT][4], dmB[KT][4];
-  encoder_out_cols<K>(layer, hid, mB, dmB);
+  encoder_out_cols<K, R>(layer, hid, mB, dmB);
   if (valid) {
     R* __restrict__ gr = static_cast<R*>(A.grad) + e * K;
     R* __restrict__ gp = static_cast<R*>(A.gprime) + e * K;

@@ -32,17 +32,13 @@ constexpr int kMonomials = 20;            // Cartesian monomials of degree <= 3
 constexpr size_t kStaticScratchBytes = size_t(256) << 20;
 constexpr size_t kStaticScratchHeader = 256;
 
-// Base-256 digits of a float64 encoder weight on the device (fused.hip).
-constexpr int kWeightDigits = 7;
-// Number of values in one packed encoder table (device layout).  float64
-// tables hold each weight matrix as digits, seven bytes per weight, with a
-// scale per row beside the bias.
+// Base-256 digits (bytes) of an encoder weight on the device (fused.hip).
+constexpr int weight_digits(int precision) { return precision == 64 ? 7 : 4; }
+// Number of values in one packed encoder table (device layout): each weight
+// matrix as digits, with a scale per row beside the bias.
 inline size_t enc_table_elems(int k, int enc_hidden, int precision) {
-  if (precision == 64)
-    return 2 * kEncWidth + size_t(enc_hidden - 1) * (kEncWidth * kEncWidth / 8 * kWeightDigits + 2 * kEncWidth) +
-           size_t(k) * kEncWidth / 8 * kWeightDigits + 2 * size_t(k);
-  return 2 * kEncWidth + size_t(enc_hidden - 1) * (kEncWidth * kEncWidth + kEncWidth) +
-         size_t(k) * kEncWidth + k;
+  const size_t row = size_t(kEncWidth) * weight_digits(precision) / (precision / 8);
+  return 2 * kEncWidth + size_t(enc_hidden - 1) * kEncWidth * (row + 2) + size_t(k) * (row + 2);
 }
 // Number of values in one packed head table (device layout).
 inline size_t head_table_elems(int nin, int reg_hidden) {
