@@ -545,7 +545,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     delete ctx;
     return create_fail(MLIP_E_ARG, err.empty() ? "weight repacking size mismatch" : "angular table: " + err);
   }
-  size_t cap = 0, cap2 = 0, cap3 = 0, cap4 = 0, cap5 = 0, cap6 = 0, cap7 = 0, cap8 = 0;
+  size_t cap = 0, cap2 = 0, cap3 = 0, cap4 = 0, cap5 = 0, cap6 = 0, cap7 = 0, cap8 = 0, cap9 = 0;
   mlip_status st = MLIP_OK;
   const size_t eb = ctx->elem_bytes;
   if ((st = ensure(ctx, &ctx->d_enc, &cap, enc.size(), "encoder")) != MLIP_OK ||
@@ -554,6 +554,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
       (st = ensure(ctx, &ctx->d_totals, &cap4, size_t(16), "totals")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_counters, &cap5, size_t(4), "counters")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_flags, &cap6, size_t(4), "flags")) != MLIP_OK ||
+      (st = ensure(ctx, &ctx->d_result, &cap9, size_t(1), "build result")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_reduce, &cap7, size_t(4), "reduce")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_inv_mass, &cap8, size_t(kMaxSpecies), "masses")) != MLIP_OK) {
     const std::string msg = ctx->err;
@@ -567,6 +568,13 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     mlip_destroy(ctx);
     return create_fail(MLIP_E_HIP, "weight upload failed");
   }
+  void* pinned = nullptr;
+  if (hipHostMalloc(&pinned, sizeof(BuildResult), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    mlip_destroy(ctx);
+    return create_fail(MLIP_E_OOM, "pinned host allocation failed: build result");
+  }
+  ctx->h_result = static_cast<BuildResult*>(pinned);
   *out = ctx;
   return MLIP_OK;
 }
@@ -645,23 +653,20 @@ mlip_status mlip_build_neighbors(mlip_ctx* ctx, int64_t n_atoms, const double* p
   MLIP_HIP(ctx, launch_fill_i32(ctx->d_flags, 4, 0, s));
   MLIP_HIP(ctx, launch_bin(pos_dev, ctx->d_types, n, g, ctx->d_key, ctx->d_cell_count, ctx->d_flags, s));
   MLIP_HIP(ctx, launch_exclusive_scan_i32_to_i32(ctx->d_cell_count, nkeys, ctx->d_cell_start, ctx->d_scan_tmp, s));
-  MLIP_HIP(ctx, launch_fill_i32(ctx->d_cell_count, nkeys + 1, 0, s));
-  MLIP_HIP(ctx, launch_scatter(ctx->d_key, n, ctx->d_cell_start, ctx->d_cell_count, ctx->d_perm, ctx->d_flags, s));
-  MLIP_HIP(ctx, launch_sort_segments(ctx->d_cell_start, nkeys, ctx->d_perm, s));
-  MLIP_HIP(ctx, launch_gather_sorted(pos_dev, ctx->d_perm, n, g, ctx->d_spos, s));
+  // the row counts' buffer holds the unordered permutation until the rows are counted
+  MLIP_HIP(ctx, launch_scatter(ctx->d_key, n, ctx->d_cell_start, ctx->d_cell_count, ctx->d_rowcnt, ctx->d_flags, s));
+  MLIP_HIP(ctx, launch_sort_gather(pos_dev, ctx->d_key, ctx->d_cell_start, ctx->d_rowcnt, n, g, ctx->d_perm,
+                                   ctx->d_spos, s));
   MLIP_HIP(ctx, launch_rows(ctx->d_spos, ctx->d_perm, n, g, ctx->d_cell_start, ctx->d_rowcnt, nullptr, nullptr,
                             ctx->d_flags, false, 0, 0, s));
   MLIP_HIP(ctx, launch_exclusive_scan_i32_to_i64(ctx->d_rowcnt, n, ctx->d_offsets, ctx->d_scan_tmp, s));
-
-  int64_t total = 0;
-  int32_t flags[4] = {0, 0, 0, 0};
-  int32_t sp[kMaxSpecies + 1];
-  MLIP_HIP(ctx, hipMemcpyAsync(&total, ctx->d_offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  MLIP_HIP(ctx, hipMemcpyAsync(flags, ctx->d_flags, sizeof(flags), hipMemcpyDeviceToHost, s));
-  for (int sp_i = 0; sp_i <= C; ++sp_i)
-    MLIP_HIP(ctx, hipMemcpyAsync(&sp[sp_i], ctx->d_cell_start + int64_t(sp_i) * ncell, sizeof(int32_t),
-                                 hipMemcpyDeviceToHost, s));
+  // one copy to pinned memory brings back everything the host needs
+  MLIP_HIP(ctx, launch_build_result(ctx->d_offsets + n, ctx->d_flags, ctx->d_cell_start, g, ctx->d_result, s));
+  MLIP_HIP(ctx, hipMemcpyAsync(ctx->h_result, ctx->d_result, sizeof(BuildResult), hipMemcpyDeviceToHost, s));
   MLIP_HIP(ctx, hipStreamSynchronize(s));
+  const int64_t total = ctx->h_result->total;
+  const int32_t* const flags = ctx->h_result->flags;
+  const int32_t* const sp = ctx->h_result->species_start;
   if (flags[0]) return fail(ctx, MLIP_E_TYPE, "species outside [0, n_species) or non-finite position");
   if (flags[1] > kEntCap) return fail(ctx, MLIP_E_NBR_CAP, "a neighbour row is longer than 2048 entries");
 
@@ -952,9 +957,10 @@ void mlip_destroy(mlip_ctx* ctx) {
   void* bufs[] = {ctx->d_enc, ctx->d_head, ctx->d_qc, ctx->d_inv_mass, ctx->d_types, ctx->d_perm,
                   ctx->d_key, ctx->d_spos, ctx->d_rowcnt, ctx->d_offsets, ctx->d_idx, ctx->d_cell_count,
                   ctx->d_cell_start, ctx->d_scan_tmp, ctx->d_ws, ctx->d_totals, ctx->d_counters,
-                  ctx->d_flags, ctx->d_reduce, ctx->d_gbuf, ctx->d_unf};
+                  ctx->d_flags, ctx->d_reduce, ctx->d_gbuf, ctx->d_unf, ctx->d_result};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
+  if (ctx->h_result) (void)hipHostFree(ctx->h_result);
   (void)hipGetLastError();
   delete ctx;
 }

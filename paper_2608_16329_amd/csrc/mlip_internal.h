@@ -148,6 +148,13 @@ struct NbrGrid {
   double rl2;
 };
 
+// What a list build reads back from the device.
+struct BuildResult {
+  int64_t total;                         // listed entries
+  int32_t flags[4];                      // bad input, longest row, largest bucket
+  int32_t species_start[kMaxSpecies + 1];
+};
+
 // Tiles of the fused kernel: centre atoms per tile, tiles, resident
 // work-groups and workspace values per work-group.
 struct TilePlan {
@@ -214,6 +221,8 @@ struct mlip_ctx {
   double* d_totals = nullptr;               // [16]
   unsigned long long* d_counters = nullptr; // [4]
   int32_t* d_flags = nullptr;               // [4]
+  mlip::BuildResult* d_result = nullptr;    // [1], and its pinned host copy
+  mlip::BuildResult* h_result = nullptr;
   double* d_reduce = nullptr;               // [4] scratch for md reductions
   int tile_atoms = 0;
   int64_t n_tiles = 0;
@@ -243,9 +252,13 @@ hipError_t launch_bin(const double* pos, const int32_t* types, int64_t n, const 
                       int32_t* key, int32_t* cell_count, int32_t* flags, hipStream_t s);
 hipError_t launch_scatter(const int32_t* key, int64_t n, const int32_t* cell_start, int32_t* fill,
                           int32_t* perm, int32_t* flags, hipStream_t s);
-hipError_t launch_sort_segments(const int32_t* cell_start, int64_t nkeys, int32_t* perm, hipStream_t s);
-hipError_t launch_gather_sorted(const double* pos, const int32_t* perm, int64_t n, const NbrGrid& g,
-                                double* spos, hipStream_t s);
+// the scattered permutation put in order within each bucket, and the wrapped
+// positions in that order
+hipError_t launch_sort_gather(const double* pos, const int32_t* key, const int32_t* cell_start,
+                              const int32_t* scattered, int64_t n, const NbrGrid& g, int32_t* perm, double* spos,
+                              hipStream_t s);
+hipError_t launch_build_result(const int64_t* total, const int32_t* flags, const int32_t* cell_start, const NbrGrid& g,
+                               BuildResult* out, hipStream_t s);
 // rows: count pass (fill false) or fill pass writing int32 indices or, with
 // tbits > 0, 16-bit codes (ListView) into idx
 hipError_t launch_rows(const double* spos, const int32_t* perm, int64_t n, const NbrGrid& g,
