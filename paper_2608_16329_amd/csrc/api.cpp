@@ -259,12 +259,18 @@ void decode_row(const mlip_ctx* ctx, const HostList& h, int64_t i, const unsigne
   for (int64_t e = 0; e < len; ++e) out[e] = h.view.perm[code_slot(h.view, cand, codes[e])];
 }
 
+// Copy n <= 16 values to the host through pinned memory (a copy to the caller's
+// pageable memory is staged by the runtime), synchronising the stream.
+mlip_status read_back(mlip_ctx* ctx, const double* dev, int n, double* host) {
+  MLIP_HIP(ctx, hipMemcpyAsync(ctx->h_back->values, dev, size_t(n) * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+  MLIP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  std::memcpy(host, ctx->h_back->values, size_t(n) * sizeof(double));
+  return MLIP_OK;
+}
+
 // Copy the totals to the host when asked (synchronising the stream).
 mlip_status finish_compute(mlip_ctx* ctx, const double* d_totals, double* totals_host) {
-  if (totals_host) {
-    MLIP_HIP(ctx, hipMemcpyAsync(totals_host, d_totals, 10 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    MLIP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  }
+  if (totals_host) MLIP_TRY(read_back(ctx, d_totals, 10, totals_host));
   return MLIP_OK;
 }
 
@@ -390,9 +396,7 @@ mlip_status run_compute(mlip_ctx* ctx, const double* pos_dev, double* energy_dev
     return MLIP_OK;
   }
   if (!pos_dev || !forces_dev) return fail(ctx, MLIP_E_ARG, "NULL positions or forces");
-  MLIP_HIP(ctx, launch_fill_f64(forces_dev, 3 * n, 0.0, s));
-  MLIP_HIP(ctx, launch_fill_f64(sc.totals, 16, 0.0, s));
-  MLIP_HIP(ctx, launch_fill_u64(sc.counters, 4, s));
+  MLIP_HIP(ctx, launch_clear_outputs(forces_dev, n, sc.totals, sc.counters, s));
 
   FusedArgs a{};
   a.pos = pos_dev;
@@ -569,12 +573,12 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     return create_fail(MLIP_E_HIP, "weight upload failed");
   }
   void* pinned = nullptr;
-  if (hipHostMalloc(&pinned, sizeof(BuildResult), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(&pinned, sizeof(HostBack), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     mlip_destroy(ctx);
-    return create_fail(MLIP_E_OOM, "pinned host allocation failed: build result");
+    return create_fail(MLIP_E_OOM, "pinned host allocation failed");
   }
-  ctx->h_result = static_cast<BuildResult*>(pinned);
+  ctx->h_back = static_cast<HostBack*>(pinned);
   *out = ctx;
   return MLIP_OK;
 }
@@ -662,11 +666,11 @@ mlip_status mlip_build_neighbors(mlip_ctx* ctx, int64_t n_atoms, const double* p
   MLIP_HIP(ctx, launch_exclusive_scan_i32_to_i64(ctx->d_rowcnt, n, ctx->d_offsets, ctx->d_scan_tmp, s));
   // one copy to pinned memory brings back everything the host needs
   MLIP_HIP(ctx, launch_build_result(ctx->d_offsets + n, ctx->d_flags, ctx->d_cell_start, g, ctx->d_result, s));
-  MLIP_HIP(ctx, hipMemcpyAsync(ctx->h_result, ctx->d_result, sizeof(BuildResult), hipMemcpyDeviceToHost, s));
+  MLIP_HIP(ctx, hipMemcpyAsync(&ctx->h_back->build, ctx->d_result, sizeof(BuildResult), hipMemcpyDeviceToHost, s));
   MLIP_HIP(ctx, hipStreamSynchronize(s));
-  const int64_t total = ctx->h_result->total;
-  const int32_t* const flags = ctx->h_result->flags;
-  const int32_t* const sp = ctx->h_result->species_start;
+  const int64_t total = ctx->h_back->build.total;
+  const int32_t* const flags = ctx->h_back->build.flags;
+  const int32_t* const sp = ctx->h_back->build.species_start;
   if (flags[0]) return fail(ctx, MLIP_E_TYPE, "species outside [0, n_species) or non-finite position");
   if (flags[1] > kEntCap) return fail(ctx, MLIP_E_NBR_CAP, "a neighbour row is longer than 2048 entries");
 
@@ -960,7 +964,7 @@ void mlip_destroy(mlip_ctx* ctx) {
                   ctx->d_flags, ctx->d_reduce, ctx->d_gbuf, ctx->d_unf, ctx->d_result};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
-  if (ctx->h_result) (void)hipHostFree(ctx->h_result);
+  if (ctx->h_back) (void)hipHostFree(ctx->h_back);
   (void)hipGetLastError();
   delete ctx;
 }
@@ -995,10 +999,7 @@ mlip_status mlip_md_first_half(mlip_ctx* ctx, double* pos_dev, double* vel_dev, 
   if (track && !ref_dev)
     MLIP_HIP(ctx, launch_md_disp_since_build(pos_dev, ctx->d_perm, ctx->d_spos, ctx->n, ctx->box, ctx->d_reduce,
                                              ctx->stream));
-  if (track) {
-    MLIP_HIP(ctx, hipMemcpyAsync(max_disp2_host, ctx->d_reduce, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    MLIP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  }
+  if (track) MLIP_TRY(read_back(ctx, ctx->d_reduce, 1, max_disp2_host));
   return MLIP_OK;
 }
 
@@ -1022,9 +1023,7 @@ mlip_status mlip_md_kinetic(mlip_ctx* ctx, const double* vel_dev, double* ke_hos
   if (!vel_dev) return fail(ctx, MLIP_E_ARG, "NULL argument");
   MLIP_HIP(ctx, launch_fill_f64(ctx->d_reduce + 1, 1, 0.0, ctx->stream));
   MLIP_HIP(ctx, launch_md_kinetic(vel_dev, ctx->d_types, ctx->d_inv_mass, ctx->n, ctx->d_reduce + 1, ctx->stream));
-  MLIP_HIP(ctx, hipMemcpyAsync(ke_host, ctx->d_reduce + 1, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  MLIP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  return MLIP_OK;
+  return read_back(ctx, ctx->d_reduce + 1, 1, ke_host);
 }
 
 }  // extern "C"

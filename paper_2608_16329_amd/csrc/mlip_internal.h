@@ -155,6 +155,12 @@ struct BuildResult {
   int32_t species_start[kMaxSpecies + 1];
 };
 
+// Pinned host memory of a context for what its calls read back.
+struct HostBack {
+  BuildResult build;
+  double values[16];                     // totals of an evaluation, or one reduced value
+};
+
 // Tiles of the fused kernel: centre atoms per tile, tiles, resident
 // work-groups and workspace values per work-group.
 struct TilePlan {
@@ -221,8 +227,8 @@ struct mlip_ctx {
   double* d_totals = nullptr;               // [16]
   unsigned long long* d_counters = nullptr; // [4]
   int32_t* d_flags = nullptr;               // [4]
-  mlip::BuildResult* d_result = nullptr;    // [1], and its pinned host copy
-  mlip::BuildResult* h_result = nullptr;
+  mlip::BuildResult* d_result = nullptr;    // [1]
+  mlip::HostBack* h_back = nullptr;         // pinned
   double* d_reduce = nullptr;               // [4] scratch for md reductions
   int tile_atoms = 0;
   int64_t n_tiles = 0;
@@ -271,7 +277,8 @@ hipError_t launch_exclusive_scan_i32_to_i64(const int32_t* in, int64_t n, int64_
 size_t scan_tmp_elems(int64_t n);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s);
-hipError_t launch_fill_u64(unsigned long long* p, int64_t n, hipStream_t s);
+// forces [n][3], totals [16] and counters [4] of an evaluation, one launch
+hipError_t launch_clear_outputs(double* forces, int64_t n, double* totals, unsigned long long* counters, hipStream_t s);
 
 // fused.hip.  k 16, 32 or 64; precision 64 or 32; angular configuration
 // acfg 0 (irreducible, l_max <= 3: 16 rows x 20 monomials), 1 (Cartesian,

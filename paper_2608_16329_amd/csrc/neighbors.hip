@@ -348,6 +348,15 @@ __global__ void k_fill(T* __restrict__ p, int64_t n, T v) {
   if (i < n) p[i] = v;
 }
 
+// Outputs and sums of an evaluation cleared in one launch.
+__global__ void k_clear_outputs(double* __restrict__ forces, int64_t n3, double* __restrict__ totals,
+                                unsigned long long* __restrict__ counters) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n3) forces[i] = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x < 16) totals[threadIdx.x] = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x < 4) counters[threadIdx.x] = 0;
+}
+
 // What the build reads back: list length, flags, and the first sorted slot of
 // each species.
 __global__ void k_build_result(const int64_t* __restrict__ total, const int32_t* __restrict__ flags,
@@ -403,9 +412,8 @@ hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fill_u64(unsigned long long* p, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  k_fill<unsigned long long><<<blocks_for(n, 256), 256, 0, s>>>(p, n, 0ull);
+hipError_t launch_clear_outputs(double* forces, int64_t n, double* totals, unsigned long long* counters, hipStream_t s) {
+  k_clear_outputs<<<blocks_for(3 * n, 256), 256, 0, s>>>(forces, 3 * n, totals, counters);
   return hipGetLastError();
 }
 
