@@ -29,7 +29,7 @@ SOURCES = [("api.cpp", "api", []), ("angular_tables.cpp", "angular_tables", []),
            ("fused.hip", "fused_f64", ["-DMLIP_FUSED_PART=1"] + VGPR_SUMS),
            ("fused.hip", "fused_f64_high", ["-DMLIP_FUSED_PART=2"] + VGPR_SUMS),
            ("fused.hip", "fused_f32", ["-DMLIP_FUSED_PART=3"]),
-           ("unfused.hip", "unfused", []), ("md.hip", "md", []), ("scratch.hip", "scratch", [])]
+           ("pack.hip", "pack", []), ("unfused.hip", "unfused", []), ("md.hip", "md", []), ("scratch.hip", "scratch", [])]
 
 
 def hipcc() -> str:

@@ -133,63 +133,6 @@ void pack_fragments(const double* M, int nout, int nin, int precision, std::vect
         }
 }
 
-// Append n values in the kernel's arithmetic type.
-void append_values(const double* v, size_t n, int precision, std::vector<unsigned char>* out) {
-  const size_t at = out->size(), eb = size_t(precision / 8);
-  out->resize(at + n * eb);
-  if (precision == 64) {
-    std::memcpy(out->data() + at, v, n * eb);
-  } else {
-    float* f = reinterpret_cast<float*>(out->data() + at);
-    for (size_t i = 0; i < n; ++i) f[i] = float(v[i]);
-  }
-}
-
-// Append a row-major [nout][128] matrix as digits for the 16x16x64 8-bit
-// integer MFMA, followed by one scale per row.  The integers of a row are
-// round(w s) = sum_i d_i 256^(D - 1 - i) with digits in [-128, 127], where s
-// takes the row's largest weight to 0.99 x 2^(8 D - 1) (balanced digits hold
-// 0.996 times that), and its scale is 2^(8 D) / s (NaN for a row with an
-// infinity or NaN, whose digits are zero).  Digit i of the half hf (columns
-// 64 hf ..) of output tile t is fragment 2 D t + D hf + i, 16 bytes at lane
-// 16 g + c: byte 4 T + q is row 16 t + c, column 64 hf + 16 T + 4 g + q.
-template <int D>
-void pack_digits(const double* M, int nout, int precision, std::vector<unsigned char>* out) {
-  constexpr int W = kEncWidth;
-  constexpr uint64_t kOffset = 0x80808080808080ull >> (8 * (7 - D));
-  const size_t at = out->size();
-  out->resize(at + size_t(nout) * W * D);
-  unsigned char* frag = out->data() + at;
-  std::vector<double> scale(static_cast<size_t>(nout));
-  for (int o = 0; o < nout; ++o) {
-    double top = 0.0;
-    bool finite = true;
-    for (int c = 0; c < W; ++c) {
-      finite = finite && std::isfinite(M[size_t(o) * W + c]);
-      top = std::max(top, std::fabs(M[size_t(o) * W + c]));
-    }
-    // the weights by an exact power of two into (-1, 1), then the scale
-    int E = 0;
-    const double lead = finite && top > 0.0 ? std::frexp(top, &E) : 1.0;
-    const double down1 = std::ldexp(1.0, -E / 2), down2 = std::ldexp(1.0, -(E - E / 2));
-    const double s = 0.99 * std::ldexp(1.0, 8 * D - 1) / lead;
-    scale[size_t(o)] = finite ? std::ldexp(std::ldexp(1.0, 8 * D) / s, E) : std::nan("");
-    for (int hf = 0; hf < 2; ++hf)
-      for (int g = 0; g < 4; ++g) {
-        unsigned char lane[D][16];
-        for (int b = 0; b < 16; ++b) {
-          const double v = finite ? M[size_t(o) * W + 64 * hf + 16 * (b / 4) + 4 * g + b % 4] * down1 * down2 * s : 0.0;
-          // an offset of 128 in every digit turns them into plain bytes
-          const uint64_t x = (uint64_t(int64_t(v + (v < 0 ? -0.5 : 0.5))) + kOffset) ^ kOffset;
-          for (int i = 0; i < D; ++i) lane[i][b] = (unsigned char)(x >> (8 * (D - 1 - i)));
-        }
-        unsigned char* p = frag + (size_t(o / 16) * 2 * D + size_t(hf) * D) * 1024 + (16 * g + o % 16) * 16;
-        for (int i = 0; i < D; ++i) std::memcpy(p + size_t(i) * 1024, lane[i], 16);
-      }
-  }
-  append_values(scale.data(), scale.size(), precision, out);
-}
-
 // Copy host values to the device in the kernel's arithmetic type.
 hipError_t upload(void* dev, const double* host, size_t n, size_t elem_bytes) {
   if (elem_bytes == sizeof(double)) return hipMemcpy(dev, host, n * sizeof(double), hipMemcpyHostToDevice);
@@ -501,28 +444,11 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   ctx->head_stride = head_table_elems(nin, hp->reg_hidden);
   ctx->elem_bytes = hp->precision == 64 ? sizeof(double) : sizeof(float);
   const int prec = hp->precision;
-  // encoder tables -> [w0 b0 | (digits(W_t) row scales b_t)... | digits(W_out)
-  // row scales b_out]
-  std::vector<unsigned char> enc;
-  enc.reserve(ctx->enc_stride * ctx->n_enc * ctx->elem_bytes);
-  const double* src = weights_host;
-  const size_t W = kEncWidth;
-  for (int t = 0; t < ctx->n_enc; ++t) {
-    const double* p = src + size_t(t) * enc_blob_doubles(hp);
-    append_values(p, 2 * W, prec, &enc);
-    p += 2 * W;
-    for (int h = 1; h <= hp->enc_hidden; ++h) {
-      const int rows = h < hp->enc_hidden ? kEncWidth : k;
-      if (prec == 64) pack_digits<weight_digits(64)>(p, rows, prec, &enc);
-      else pack_digits<weight_digits(32)>(p, rows, prec, &enc);
-      append_values(p + size_t(rows) * W, size_t(rows), prec, &enc);
-      p += size_t(rows) * W + size_t(rows);
-    }
-  }
   // head tables -> [frag(A0) | frag(A0^T) | c0 | (frag(A_t) frag(A_t^T) c_t)... | a_out c_out]
   std::vector<double> head;
   head.reserve(ctx->head_stride * ctx->n_head);
-  const double* hsrc = src + size_t(ctx->n_enc) * enc_blob_doubles(hp);
+  const size_t enc_values = size_t(ctx->n_enc) * enc_blob_doubles(hp);
+  const double* hsrc = weights_host + enc_values;
   const int R = kHeadWidth;
   for (int t = 0; t < ctx->n_head; ++t) {
     const double* p = hsrc + size_t(t) * head_blob_doubles(hp);
@@ -544,7 +470,6 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   std::vector<double> qc;
   std::string err;
   if (!build_angular_table(hp->lmax, hp->angular, qrows, qcols, &qc, ctx->lrow, &err) ||
-      enc.size() != ctx->enc_stride * ctx->n_enc * ctx->elem_bytes ||
       head.size() != ctx->head_stride * ctx->n_head) {
     delete ctx;
     return create_fail(MLIP_E_ARG, err.empty() ? "weight repacking size mismatch" : "angular table: " + err);
@@ -552,7 +477,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   size_t cap = 0, cap2 = 0, cap3 = 0, cap4 = 0, cap5 = 0, cap6 = 0, cap7 = 0, cap8 = 0, cap9 = 0;
   mlip_status st = MLIP_OK;
   const size_t eb = ctx->elem_bytes;
-  if ((st = ensure(ctx, &ctx->d_enc, &cap, enc.size(), "encoder")) != MLIP_OK ||
+  if ((st = ensure(ctx, &ctx->d_enc, &cap, ctx->enc_stride * size_t(ctx->n_enc) * eb, "encoder")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_head, &cap2, head.size() * eb, "head")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_qc, &cap3, qc.size() * eb, "tables")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_totals, &cap4, size_t(16), "totals")) != MLIP_OK ||
@@ -565,7 +490,21 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
     mlip_destroy(ctx);
     return create_fail(st, msg);
   }
-  if (hipMemcpy(ctx->d_enc, enc.data(), enc.size(), hipMemcpyHostToDevice) != hipSuccess ||
+  // encoder tables -> [w0 b0 | (digits(W_t) row scales b_t)... | digits(W_out)
+  // row scales b_out], formed on the device from a copy of the blob
+  double* blob = nullptr;
+  if (hipMalloc(reinterpret_cast<void**>(&blob), enc_values * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    mlip_destroy(ctx);
+    return create_fail(MLIP_E_OOM, "device allocation failed: weights");
+  }
+  const bool packed =
+      hipMemcpy(blob, weights_host, enc_values * sizeof(double), hipMemcpyHostToDevice) == hipSuccess &&
+      launch_pack_encoder(blob, ctx->n_enc, hp->enc_hidden, k, prec, ctx->d_enc, ctx->enc_stride, nullptr) ==
+          hipSuccess &&
+      hipStreamSynchronize(nullptr) == hipSuccess;
+  (void)hipFree(blob);
+  if (!packed ||
       upload(ctx->d_head, head.data(), head.size(), eb) != hipSuccess ||
       upload(ctx->d_qc, qc.data(), qc.size(), eb) != hipSuccess) {
     (void)hipGetLastError();

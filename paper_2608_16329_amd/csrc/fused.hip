@@ -454,11 +454,11 @@ template <typename R>
 struct Split;
 template <>
 struct Split<double> {
-  static constexpr int W = 7, D = 7, S = 7;  // digits of weights and activations, sums (i + j < S)
+  [[maybe_unused]] static constexpr int W = 7, D = 7, S = 7;  // digits of weights and activations, sums (i + j < S)
 };
 template <>
 struct Split<float> {
-  static constexpr int W = 4, D = 3, S = 4;
+  [[maybe_unused]] static constexpr int W = 4, D = 3, S = 4;
 };
 static_assert(Split<double>::W == weight_digits(64) && Split<float>::W == weight_digits(32), "packed digits");
 typedef int v4i __attribute__((ext_vector_type(4)));

@@ -253,6 +253,11 @@ namespace mlip {
 bool build_angular_table(int lmax, int angular, int rows, int cols, std::vector<double>* out, int lrow[8],
                          std::string* err);
 
+// pack.hip: encoder tables (enc_table_elems values each, stride apart) from the
+// caller's blob
+hipError_t launch_pack_encoder(const double* blob, int tables, int hidden, int k, int precision, void* out, size_t stride,
+                               hipStream_t s);
+
 // neighbors.hip
 hipError_t launch_bin(const double* pos, const int32_t* types, int64_t n, const NbrGrid& g,
                       int32_t* key, int32_t* cell_count, int32_t* flags, hipStream_t s);
