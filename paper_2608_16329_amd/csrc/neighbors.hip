@@ -128,6 +128,7 @@ __global__ void k_sort_gather(const double* __restrict__ pos, const int32_t* __r
 constexpr int kRowThreads = 256;
 constexpr int kRowCand = 1024;   // candidates staged at a time
 constexpr int kRowAtoms = 64;    // centre atoms handled at a time
+constexpr int kRowCellsX = 1 << 22;  // work-groups along x
 constexpr int kMaxRuns = 27 * kMaxSpecies;
 
 // Exclusive prefix of run lengths len[0 .. n) into first[0 .. n] (n <= 2
@@ -163,7 +164,10 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(const double* __restrict__
   __shared__ int afirst[kMaxSpecies + 1];  // centre atoms before each species
   __shared__ int cnt[kRowAtoms];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cell = blockIdx.x;
+  // cells along x, layer by layer along z
+  const int64_t block = int64_t(blockIdx.z) * gridDim.x + blockIdx.x;
+  if (block >= g.ncell) return;
+  const int cell = int(block);
   const int cc[3] = {cell % g.nc[0], cell / g.nc[0] % g.nc[1], cell / (g.nc[0] * g.nc[1])};
   int xs[3], ys[3], zs[3];
   const int nx = adjacent(cc[0], g.nc[0], xs), ny = adjacent(cc[1], g.nc[1], ys), nz = adjacent(cc[2], g.nc[2], zs);
@@ -449,7 +453,11 @@ hipError_t launch_rows(const double* spos, const int32_t* perm, int64_t n, const
   // until there are about two per compute unit
   const int64_t per_cell = (n + g.ncell - 1) / g.ncell;
   const int64_t split = std::max<int64_t>(1, std::min<int64_t>((512 + g.ncell - 1) / g.ncell, (per_cell + 3) / 4));
-  const dim3 grid(unsigned(g.ncell), unsigned(std::min<int64_t>(split, 65535)));
+  // a launch takes at most 2^32 - 1 threads along a dimension, which work-groups
+  // of 256 for every cell pass from 16.8 million cells (about 290 million BCC
+  // atoms); cells past kRowCellsX go to the next layer
+  const unsigned across = unsigned(std::min<int64_t>(g.ncell, kRowCellsX));
+  const dim3 grid(across, unsigned(std::min<int64_t>(split, 65535)), unsigned((int64_t(g.ncell) + across - 1) / across));
   if (!fill)
     k_rows<false, false><<<grid, kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets, idx, flags, 0, 0);
   else if (tbits > 0)

@@ -56,3 +56,24 @@ def test_longest_row_and_total():
     pot.close()
     assert st["max_row"] == max(len(r) for r in rows)
     assert st["n_listed_pairs"] == sum(len(r) for r in rows)
+
+
+def test_more_cells_than_one_launch_dimension():
+    """Work-groups of 256 threads for each of 17 million cells are more threads
+    than a launch dimension takes."""
+    from paper_2608_16329_amd import Potential
+    rng = np.random.default_rng(6)
+    n, edge = 4_300_000, 1672.0
+    box = np.full(3, edge)
+    pos = np.repeat(rng.uniform(0.0, edge, (n // 4, 3)), 4, axis=0) + rng.normal(0.0, 1.5, (n, 3))
+    hp = synth.HParams(n_species=1)
+    pot = Potential(hp, synth.random_weights(hp, 1))
+    pot.build_neighbors(to_dev(pos), to_dev(np.zeros(n, np.int32)), box)
+    st = pot.stats()
+    log(f"[rows] {n} atoms, {st['n_cells']} cells")
+    assert st["n_cells"] * 256 > 2**32
+    atoms = np.argsort(pos[:, 2])[np.linspace(0, n - 1, 25).astype(np.int64)]
+    got = pot.neighbor_rows(atoms)
+    pot.close()
+    compare_rows(got, neighbors_of(pos, box, hp.cutoff + hp.skin, atoms), atoms)
+    assert sum(len(r) for r in got) >= 50
