@@ -441,12 +441,14 @@ __device__ __forceinline__ int hrow(int q, int g) { return 4 * g + q; }
 // cycles at 2.1 GHz, 28 us, instead of 91 thousand at 2.34 GHz, 39 us; the
 // kernel 198.6 ms instead of 251.0 ms at 1,048,576 atoms of six species.
 //
-// float32: weights of four digits, activations of three (24 bits), the nine
-// digit products with i + j <= 3 (with three digits both, and still more with
-// six products, the outputs were further from float64 than with float32
-// MFMAs): 3.42e-7, 1.51e-6 and 1.38e-6 of E, F and w at 1,048,576 atoms,
-// 3.45e-7, 1.58e-6 and 1.44e-6 with float32 MFMAs.  List and evaluation of
-// these atoms take 90 ms instead of 132.
+// float32: four digits (32 bits) of both, the ten digit products with i + j
+// <= 3.  Three digits of an activation (24 bits under the column's scale, nine
+// products) are 1.3% faster (35.19 against 35.65 ms at 442,368 atoms), but
+// values below the column's largest then have fewer bits than float32 gives
+// them: with one hidden unit 100 times the others (and its weights in the next
+// layers 1/100) forces were off by 8.4e-6, 1.1e-6 with float32 MFMAs and 9.8e-7
+// with four digits.  With ordinary weights (131,072 atoms, six species) 1.39e-6,
+// 1.60e-6 with float32 MFMAs.
 //
 // What bounds it is vector issue: about 76 (float64) and 40 (float32) vector
 // instructions per activation and tangent beside 28 and 9 MFMAs.
@@ -458,7 +460,7 @@ struct Split<double> {
 };
 template <>
 struct Split<float> {
-  [[maybe_unused]] static constexpr int W = 4, D = 3, S = 4;
+  [[maybe_unused]] static constexpr int W = 4, D = 4, S = 4;
 };
 static_assert(Split<double>::W == weight_digits(64) && Split<float>::W == weight_digits(32), "packed digits");
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -480,8 +482,9 @@ struct Digits {
 // and its column's four lanes) to just below 0.99 x 2^23: the closer to the
 // full range, the less the digit products that are left out weigh.  A column
 // with an infinity or NaN gets a NaN inverse, so everything formed from it is
-// NaN; one of zeros (or below 2^-974, in float32 2^-100) gets scale and inverse
-// zero.
+// NaN; one of zeros (or below 2^-974, in float32 2^-92) gets scale and inverse
+// zero.  In float32 the scale returned is that of all four digits, 2^8 times
+// as large.
 __device__ __forceinline__ int top_bits(double x) { return __double2hiint(x); }
 __device__ __forceinline__ int top_bits(float x) { return __float_as_int(x); }
 template <typename R>
@@ -514,7 +517,7 @@ __device__ __forceinline__ R digit_scale(const R (&h)[8][4], Digits<R>& d) {
     const float top = __int_as_float(int(m));
     scale = float(kRange) * __builtin_amdgcn_rcpf(top);
     inv = top * float(1.0 / kRange);
-    low = 0x0d800000u, high = 0x7e800000u;
+    low = 0x11800000u, high = 0x7e800000u;
   }
   inv = fma(fma(-scale, inv, R(1)), inv, inv);
   if (m - low >= high - low) {
@@ -522,7 +525,17 @@ __device__ __forceinline__ R digit_scale(const R (&h)[8][4], Digits<R>& d) {
     inv = m >= high ? R(__builtin_nanf("")) : R(0);
   }
   d.inv = inv;
-  return scale;
+  return sizeof(R) == 8 ? scale : scale * R(256);
+}
+
+// 4 x 4 byte transpose: byte q of out[i] is byte i of x[q].
+__device__ __forceinline__ void transpose4(const unsigned (&x)[4], unsigned (&out)[4]) {
+  const unsigned a = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), b = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
+  const unsigned e = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u), f = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(f, e, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(f, e, 0x07060302u);
 }
 
 // Digits of the half hf of a lane's values (tiles 4 hf .. 4 hf + 3): the value
@@ -554,13 +567,12 @@ __device__ __forceinline__ void make_digits(const double (&h)[8][4], double scal
     // 4 x 4 byte transposes
     const unsigned a = __builtin_amdgcn_perm(hw[1], hw[0], 0x05010400u), b = __builtin_amdgcn_perm(hw[3], hw[2], 0x05010400u);
     const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
-    const unsigned p = __builtin_amdgcn_perm(lw[1], lw[0], 0x07030602u), q = __builtin_amdgcn_perm(lw[3], lw[2], 0x07030602u);
-    const unsigned r = __builtin_amdgcn_perm(lw[1], lw[0], 0x05010400u), z = __builtin_amdgcn_perm(lw[3], lw[2], 0x05010400u);
-    const unsigned w[7] = {
-        __builtin_amdgcn_perm(f, e, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u),
-        __builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(q, p, 0x07060302u),
-        __builtin_amdgcn_perm(q, p, 0x05040100u), __builtin_amdgcn_perm(z, r, 0x07060302u),
-        __builtin_amdgcn_perm(z, r, 0x05040100u)};
+    unsigned l[4];
+    transpose4(lw, l);
+    const unsigned w[7] = {__builtin_amdgcn_perm(f, e, 0x05040100u),
+                           __builtin_amdgcn_perm(b, a, 0x07060302u),
+                           __builtin_amdgcn_perm(b, a, 0x05040100u),
+                           l[3], l[2], l[1], l[0]};
 #pragma unroll
     for (int i = 0; i < 7; ++i) d.s[i][hf][t] = int(w[i] ^ 0x80808080u);
   }
@@ -568,18 +580,18 @@ __device__ __forceinline__ void make_digits(const double (&h)[8][4], double scal
 #pragma unroll
   for (int i = 0; i < 7; ++i) asm("" : "+a"(d.s[i][hf]));
 }
-// float32: the three digits of the value rounded to an integer.
+// float32: the four digits of the value cut to an integer (24 bits of the
+// largest values, so only those below 2^-7 of the column's largest lose any,
+// at most 2^-31 of it).
 __device__ __forceinline__ void make_digits(const float (&h)[8][4], float scale, int hf, Digits<float>& d) {
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    unsigned hw[4];
+    unsigned x[4], w[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) hw[q] = unsigned(int(__builtin_rintf(h[4 * hf + t][q] * scale))) + 0x808080u;
-    const unsigned a = __builtin_amdgcn_perm(hw[1], hw[0], 0x05010400u), b = __builtin_amdgcn_perm(hw[3], hw[2], 0x05010400u);
-    const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
-    d.s[0][hf][t] = int(__builtin_amdgcn_perm(f, e, 0x05040100u) ^ 0x80808080u);
-    d.s[1][hf][t] = int(__builtin_amdgcn_perm(b, a, 0x07060302u) ^ 0x80808080u);
-    d.s[2][hf][t] = int(__builtin_amdgcn_perm(b, a, 0x05040100u) ^ 0x80808080u);
+    for (int q = 0; q < 4; ++q) x[q] = unsigned(int(h[4 * hf + t][q] * scale)) + 0x80808080u;
+    transpose4(x, w);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d.s[i][hf][t] = int(w[3 - i] ^ 0x80808080u);
   }
 }
 template <typename R>
@@ -592,7 +604,7 @@ __device__ __forceinline__ void make_digits(const R (&h)[8][4], Digits<R>& d) {
 // Sum of the digit products, S[d] = sum over i + j = d:
 // 2^8 sum_d S[d] 2^(-8d), exact up to the last rounding (float64: and to 2^-40
 // of a unit of S[0]; float32: up to the rounding of the two merged sums).  The
-// pairs that are merged as integers stay below 2^31.
+// pairs that are merged as integers stay below 2^31 (at most 1.62e9).
 __device__ __forceinline__ double digit_sum(const v4i (&S)[7], int q) {
   const int a = (S[0][q] << 8) + S[1][q], b = (S[2][q] << 8) + S[3][q], e = S[5][q] + (S[6][q] >> 8);
   double t = fma(double(S[4][q]), 0x1p-8, double(b));
@@ -647,7 +659,7 @@ struct Hidden {
 };
 
 // Products of half a 16-row weight tile (columns 64 hf .., fragments w[W hf ..])
-// with the digits x of 16 columns: 28 MFMAs in float64, 9 in float32.  With kNext each fragment's
+// with the digits x of 16 columns: 28 MFMAs in float64, 10 in float32.  With kNext each fragment's
 // registers take the fragment at next + f of the stream after its last use,
 // half a tile of products before that one is needed.  kRows: the activation
 // columns are the rows of the result.

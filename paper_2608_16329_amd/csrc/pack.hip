@@ -2,10 +2,13 @@
 // as they are, each weight matrix as digits for the 16x16x64 8-bit integer MFMA
 // (fused.hip) with one scale per row, and the biases.
 //
-// The integers of a row are round(w s) = sum_i d_i 256^(D - 1 - i) with digits
-// in [-128, 127], where s takes the row's largest weight to 0.99 x 2^(8 D - 1)
-// (balanced digits hold 0.996 times that); the row's scale is 2^(8 D) / s, NaN
-// for a row with an infinity or NaN, whose digits are zero.  Digit i of the half
+// The integers of a row are round(w 2^(8 D) / scale) = sum_i d_i 256^(D - 1 - i)
+// with digits in [-128, 127], where the row's scale takes its largest weight to
+// 0.99 x 2^(8 D - 1) (balanced digits hold 0.996 times that) and is rounded to
+// the type it is stored in first: rounded after the integers are formed, all
+// 128 weights of a row would share its rounding error, which does not average
+// over pairs and atoms.  It is NaN for a row with an infinity or NaN, whose
+// digits are zero.  Digit i of the half
 // hf (columns 64 hf ..) of output tile t is fragment 2 D t + D hf + i, 16 bytes at
 // lane 16 g + c: byte 4 T + q is row 16 t + c, column 64 hf + 16 T + 4 g + q.
 #include "mlip_internal.h"
@@ -48,15 +51,18 @@ __global__ __launch_bounds__(W) void k_pack_encoder(const double* __restrict__ b
   __syncthreads();
   top = part[0] > part[1] ? part[0] : part[1];
   const bool finite = top < 0x7ff0000000000000ull;
-  // the weights by an exact power of two into (-1, 1), then the scale
+  // the row's largest weight by an exact power of two into [0.5, 1), then its
+  // scale; the integer in two steps, since beyond 2^53 a product is rounded
   int E = 0;
   double lead = 1.0;
   if (finite && top > 0) lead = frexp(__longlong_as_double(static_cast<long long>(top)), &E);
-  const double s = 0.99 * ldexp(1.0, 8 * D - 1) / lead;
-  const double v = finite ? ldexp(w, -E) * s : 0.0;
+  const R scale = R(ldexp(lead * (2.0 / 0.99), E));
+  const double unit = ldexp(double(R(lead * (2.0 / 0.99))), -8 * D), v = finite ? ldexp(w, -E) : 0.0;
+  const double first = rint(v / unit);
+  const long long X = static_cast<long long>(first) + llrint(fma(-first, unit, v) / unit);
   // an offset of 128 in every digit turns them into plain bytes
   constexpr unsigned long long kOffset = 0x80808080808080ull >> (8 * (7 - D));
-  const unsigned long long x = (static_cast<unsigned long long>(llrint(v)) + kOffset) ^ kOffset;
+  const unsigned long long x = (static_cast<unsigned long long>(X) + kOffset) ^ kOffset;
   const int hf = c / 64, T = c % 64 / 16, g = c % 16 / 4, q = c % 4;
   unsigned char* p = reinterpret_cast<unsigned char*>(to) + (size_t(o / 16) * 2 * D + size_t(hf) * D) * 1024 +
                      (16 * g + o % 16) * 16 + 4 * T + q;
@@ -64,7 +70,7 @@ __global__ __launch_bounds__(W) void k_pack_encoder(const double* __restrict__ b
   for (int i = 0; i < D; ++i) p[i * 1024] = static_cast<unsigned char>(x >> (8 * (D - 1 - i)));
   if (c == 0) {
     R* const tail = to + size_t(nout) * W * D / sizeof(R);
-    tail[o] = finite ? R(ldexp(ldexp(1.0, 8 * D) / s, E)) : R(__builtin_nan(""));
+    tail[o] = finite ? scale : R(__builtin_nan(""));
     tail[nout + o] = R(m[size_t(nout) * W + o]);
   }
 }

@@ -7,7 +7,7 @@ Bound: a product's rounding is below 128 x 2^-53 of (largest weight of the
 row) x (largest activation of the column), 1.4e-14; the outputs pass through
 three such layers and sums of partial forces that cancel by at most about ten,
 so they agree with the oracle to 1e-12 of an output's largest value.  float32
-holds 24 bits of an activation: 128 x 2^-24 and the same factor, 1e-4."""
+sums are rounded to 24 bits: 128 x 2^-24 and the same factor, 1e-4."""
 import numpy as np
 import pytest
 
@@ -84,6 +84,44 @@ def test_digits_match_oracle(change, k, fusion, precision):
         err = np.abs(got[key] - ref[key]).max() / scale
         log(f"[digits] {change.__name__} k={k} {key}: {err:.2e}")
         assert err <= TOL[precision], (key, err)
+
+
+def _large_unit(layer, factor):
+    """One hidden unit made `factor` times as large where it is formed (layer 0:
+    the first one, 1: the second) and its weights in the layers after it 1/factor
+    times: about the same outputs."""
+    def change(name, v):
+        if not name.startswith("enc"):
+            return
+        segment = name.split(".")[1]
+        if segment == ("w0", "W1")[layer]:
+            v.reshape(128, -1)[7] *= factor
+        elif segment == ("b0", "b1")[layer]:
+            v[7] *= factor
+        elif segment in (("W1", "W2", "Wout"), ("W2", "Wout"))[layer]:
+            v.reshape(-1, 128)[:, 7] /= factor
+    return change
+
+
+# Floating-point products do not care about such a unit: their outputs differ
+# from float64 by up to 2.6e-6 (float32) of their 2-norm whatever the factor.
+# Allowed: twice that.
+NORM = {32: 5.2e-6}
+
+
+@pytest.mark.parametrize("layer", [0, 1])
+@pytest.mark.parametrize("precision,factor", [(32, 1.0), (32, 30.0), (32, 100.0)])
+def test_units_of_unequal_size(precision, factor, layer):
+    w = synth.make_workload("fcc-binary-4", seed=31, hp_overrides={"precision": precision})
+    weights = _edit(w.hp, w.weights, _large_unit(layer, factor))
+    ref = evaluate(Model(w.hp, weights), w.pos, w.types, w.box)
+    log(f"[digits] unit of layer {layer} x {factor:g} float{precision}")
+    got = gpu_eval(w.hp, weights, w.pos, w.types, w.box)
+    got["pot"].close()
+    for key in ("E_i", "F", "virial"):
+        err = np.linalg.norm(got[key] - ref[key]) / np.linalg.norm(ref[key])
+        log(f"[digits] {key}: {err:.2e}")
+        assert err <= NORM[precision], (key, err)
 
 
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
