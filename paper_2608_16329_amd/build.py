@@ -24,11 +24,14 @@ ARCH = "gfx950"
 # kernel of 512 registers is the accumulation file).
 VGPR_SUMS = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 # (source, object, further flags); the fused kernel's instantiations are built
-# in three parts
+# in six parts
 SOURCES = [("api.cpp", "api", []), ("angular_tables.cpp", "angular_tables", []), ("neighbors.hip", "neighbors", []),
-           ("fused.hip", "fused_f64", ["-DMLIP_FUSED_PART=1"] + VGPR_SUMS),
-           ("fused.hip", "fused_f64_high", ["-DMLIP_FUSED_PART=2"] + VGPR_SUMS),
-           ("fused.hip", "fused_f32", ["-DMLIP_FUSED_PART=3"]),
+           ("fused.hip", "fused_f64_digits", ["-DMLIP_FUSED_PART=1", "-DMLIP_FUSED_DIGITS=1"] + VGPR_SUMS),
+           ("fused.hip", "fused_f64_high_digits", ["-DMLIP_FUSED_PART=2", "-DMLIP_FUSED_DIGITS=1"] + VGPR_SUMS),
+           ("fused.hip", "fused_f32_digits", ["-DMLIP_FUSED_PART=3", "-DMLIP_FUSED_DIGITS=1"]),
+           ("fused.hip", "fused_f64_float", ["-DMLIP_FUSED_PART=1", "-DMLIP_FUSED_DIGITS=0"]),
+           ("fused.hip", "fused_f64_high_float", ["-DMLIP_FUSED_PART=2", "-DMLIP_FUSED_DIGITS=0"]),
+           ("fused.hip", "fused_f32_float", ["-DMLIP_FUSED_PART=3", "-DMLIP_FUSED_DIGITS=0"]),
            ("pack.hip", "pack", []), ("unfused.hip", "unfused", []), ("md.hip", "md", []), ("scratch.hip", "scratch", [])]
 
 

@@ -12,8 +12,8 @@
 //   B. Pass 1, one chunk per wavefront at a time: the radial encoder (Eq. 2)
 //      and its derivative in r run as MFMA products with the 16 pairs as one
 //      matrix dimension, the activation and its tangent as two column tiles
-//      sharing every weight fragment (float64: error-free on 8-bit integer
-//      digits, below; float32: 16x16x4).  The
+//      sharing every weight fragment (8-bit integer digits of both operands,
+//      below, or 16x16x4 floating-point products).  The
 //      moment P_i = sum_j g_ang (x) g_rad (Eq. 4) is another MFMA product
 //      (K = pairs), accumulated into LDS.  The pre-cutoff output m and its
 //      tangent dm (2k values per pair) go to a fixed-size per-work-group
@@ -46,14 +46,20 @@
 // of the encoder takes 16 bytes per lane (A[c][16g ..], B[16g ..][c]) and
 // returns row 4g + q in both precisions.
 //
-// The file is compiled in three parts (MLIP_FUSED_PART), whose instantiations
-// build in parallel: 1 float64 to l_max 3 and the entry, 2 float64 with l_max
-// 4..5, 3 float32.
+// The file is compiled in six parts, whose instantiations build in parallel:
+// MLIP_FUSED_PART 1 float64 to l_max 3, 2 float64 with l_max 4..5, 3 float32,
+// each with the encoder on 8-bit integer digits (MLIP_FUSED_DIGITS 1) and on
+// floating-point products (0), which a context takes when its weights are such
+// that digits would lose accuracy.
+#include <type_traits>
+
 #include "kernel_math.h"
 #include "mlip_internal.h"
 
 namespace mlip {
 namespace {
+
+constexpr bool kDigits = MLIP_FUSED_DIGITS;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -78,12 +84,12 @@ __device__ __forceinline__ v4f mfma(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Result row held in register q of a lane of group g, and its inverse: row c
-// sits in register qof(c) of the lanes of group gof(c).
+// Result row held in register q of a lane of group g.
 template <typename R>
 __device__ __forceinline__ int drow(int q, int g) {
   return sizeof(R) == 8 ? 4 * q + g : 4 * g + q;
 }
+
 // Logistic sigmoid 1 / (1 + exp(-z)) in float64, written out so that the
 // vector instructions are few (they, not the matrix products, bound the
 // encoder):
@@ -417,10 +423,25 @@ struct RowStream {
   }
 };
 
-// Row of the encoder's hidden activations held in register q of a lane of
-// group g, within a 16-row tile (both types), and the order in which pass 2
-// contracts the columns of m.
-__device__ __forceinline__ int hrow(int q, int g) { return 4 * g + q; }
+// Row of the encoder's outputs held in register q of a lane of group g, within
+// a 16-row tile (with pairs as rows: the pair), and the order in which pass 2
+// contracts the columns of m: the integer products return row 4g + q in both
+// precisions, floating-point ones drow(q, g).  Row c sits in register hreg(c)
+// of the lanes of group hgroup(c).
+template <typename R>
+constexpr bool kRowsByGroup = kDigits || sizeof(R) == 4;
+template <typename R>
+__device__ __forceinline__ int hrow(int q, int g) {
+  return kRowsByGroup<R> ? 4 * g + q : 4 * q + g;
+}
+template <typename R>
+__device__ __forceinline__ int hgroup(int c) {
+  return kRowsByGroup<R> ? c >> 2 : c & 3;
+}
+template <typename R>
+__device__ __forceinline__ int hreg(int c) {
+  return kRowsByGroup<R> ? c & 3 : c >> 2;
+}
 
 // ---- products on the 8-bit integer matrix pipe ------------------------------
 // A float64 MFMA runs at the rate of float64 FMAs and holds the vector pipe
@@ -736,7 +757,7 @@ __device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Sme
   for (int T = 0; T < 8; ++T)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int in = 16 * T + hrow(i, g);
+      const int in = 16 * T + 4 * g + i;
       const R w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
       const R s = sigmoid(z, kc);
       h[T][i] = z * s;
@@ -846,8 +867,8 @@ __device__ __forceinline__ void encoder_out_rows(const R* __restrict__ layer, co
   R inv[4], dinv[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    inv[q] = __shfl(in.h.inv, hrow(q, g), 64);
-    if constexpr (kTan) dinv[q] = __shfl(in.dh.inv, hrow(q, g), 64);
+    inv[q] = __shfl(in.h.inv, 4 * g + q, 64);
+    if constexpr (kTan) dinv[q] = __shfl(in.dh.inv, 4 * g + q, 64);
   }
 #pragma unroll
   for (int Tc = 0; Tc < KT; ++Tc) {
@@ -892,10 +913,272 @@ __device__ __forceinline__ void encoder_out_cols(const R* __restrict__ layer, co
   }
 }
 
-// Pair whose row of the float64 feature product this lane's column c = 4q + g
-// becomes: register q of the encoder's output holds pair 4g + q.
-__device__ __forceinline__ int moment_pair(int c, double) { return 4 * (c & 3) + (c >> 2); }
-__device__ __forceinline__ int moment_pair(int c, float) { return c; }
+// ---- the encoder on floating-point products ---------------------------------
+// For weights whose terms the digits would not hold (digits_hold in api.cpp):
+// 16x16x4 MFMAs of the network's type, the activation and its tangent sharing
+// every weight fragment.  A float64 one holds the vector pipe for its duration,
+// so products and activation functions add up: 1,048,576 atoms of six species
+// take 252.4 ms instead of 201.4, in float32 119.5 instead of 84.
+//
+// Fragments of VW consecutive output tiles per 16-byte load stream through
+// register rings issued kRing - 1 (hidden layers) or kRingO - 1 (output layer)
+// k-steps ahead of the MFMAs that consume them.  An output-layer k-step is
+// only 2 KT products, so its ring runs further ahead.  The float32 kernel runs
+// two wavefronts per SIMD, which cover each other's load latency; there
+// shallower rings leave more registers and measured faster (ring depths 2 and
+// 4 against 3 and 8).
+template <int K, typename R>
+struct Stream {
+  static constexpr int KT = K / 16;
+  static constexpr int VW = 16 / int(sizeof(R));  // fragments per load
+  static constexpr int NH = 8 / VW;               // loads per hidden-layer k-step
+  static constexpr int VO = KT < VW ? KT : VW;    // fragments per output-layer load
+  static constexpr int NO = KT / VO;              // loads per output-layer k-step
+  static constexpr int kRing = sizeof(R) == 8 ? 3 : 2;
+  static constexpr int kRingO = sizeof(R) == 8 ? 8 : 4;
+  typedef R vh_t __attribute__((ext_vector_type(VW)));
+  typedef R vo_t __attribute__((ext_vector_type(VO)));
+};
+
+// Bias vector of a hidden layer at a wave-uniform address, read through a
+// buffer descriptor in the accumulator row order: element (To, q) of lane
+// (g, c) is row 16 To + drow(q, g); the lane part of that offset is one
+// fixed vector register, the rest a scalar offset.  With bytes = 0 every
+// read returns zero without touching memory.
+template <typename R>
+struct BiasStream {
+  __amdgpu_buffer_rsrc_t rs;
+  int lo;
+  __device__ __forceinline__ BiasStream(const void* base, int bytes, int g)
+      : rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRawBufferConfig)),
+        lo((sizeof(R) == 8 ? g : 4 * g) * int(sizeof(R))) {}
+  __device__ __forceinline__ R operator()(int To, int q) const {
+    const int so = (16 * To + (sizeof(R) == 8 ? 4 * q : q)) * int(sizeof(R));
+    if constexpr (sizeof(R) == 8) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, lo, so, 0));
+    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, lo, so, 0));
+  }
+};
+
+// What the hidden layers leave for the output layer: rows 16T + drow(i, g) of
+// column c.
+template <typename R>
+struct FloatHidden {
+  R h[8][4], dh[8][4];
+};
+
+// Encoder forward and tangent up to the last hidden layer, as above, with the
+// hidden layers as 8 x 32 MFMA steps.
+template <int K, int TM, typename R, int NW, int DR, int NM, bool kTan = true>
+__device__ __forceinline__ const R* encoder_hidden(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM>& S, int sj, R r,
+                                                   const R* __restrict__ tab, FloatHidden<R>& out) {
+  typedef Stream<K, R> St;
+  typedef typename St::vh_t vh_t;
+  constexpr int NH = St::NH, VW = St::VW, kRing = St::kRing;
+  const int lane = phase_tid() & 63, g = lane >> 4;
+  const typename SigmoidOf<R>::Const kc;
+  R (&h)[8][4] = out.h;
+  R (&dh)[8][4] = out.dh;
+  constexpr int kLayerBytes = int(kEncWidth * kEncWidth * sizeof(R));
+  constexpr int kBiasBytes = int(kEncWidth * sizeof(R));
+  const int nh = A.enc_hidden;
+  // The first hidden layer's leading weight fragments are requested before
+  // the elementwise first layer, whose activation work covers their
+  // latency; each hidden layer requests the next one's in its last k-steps,
+  // so they arrive during its own activation phase.  Past the last hidden
+  // layer that descriptor has size 0 and reads zeros.  At k = 64 the wider
+  // output tiles leave no registers for fragments held across an activation
+  // phase (it measured slower): there each layer fills its ring at its start.
+  constexpr bool kCross = K <= 32;
+  const R* __restrict__ layer = tab + 2 * kEncWidth;
+  vh_t wb[kRing][NH];
+  v4<R> acc[8], dacc[8];
+  if constexpr (kCross) {
+    const FragStream<vh_t> frag(layer, nh > 1 ? kLayerBytes : 0);
+#pragma unroll
+    for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+      for (int u = 0; u < NH; ++u) wb[p][u] = frag[p * NH + u];
+  }
+#pragma unroll
+  for (int T = 0; T < 8; ++T)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int in = 16 * T + drow<R>(i, g);
+      const R w0 = S.u.p1.l0[sj][0][in], z = w0 * r + S.u.p1.l0[sj][1][in];
+      const R s = sigmoid(z, kc);
+      h[T][i] = z * s;
+      if constexpr (kTan) dh[T][i] = silu_slope(z, s) * w0;
+    }
+  for (int t = 1; t < nh; ++t) {
+    const FragStream<vh_t> frag(layer, kLayerBytes);
+    const R* __restrict__ next = layer + kEncWidth * kEncWidth + kEncWidth;
+    const bool more = t + 1 < nh;
+    const FragStream<vh_t> nfrag(next, more ? kLayerBytes : 0);
+    if constexpr (!kCross) {
+#pragma unroll
+      for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+        for (int u = 0; u < NH; ++u) wb[p][u] = frag[p * NH + u];
+    }
+    // the tangent has no bias
+    {
+      const BiasStream<R> bias(layer + kEncWidth * kEncWidth, kBiasBytes, g);
+#pragma unroll
+      for (int To = 0; To < 8; ++To) acc[To] = v4<R>{bias(To, 0), bias(To, 1), bias(To, 2), bias(To, 3)};
+    }
+#pragma unroll
+    for (int To = 0; To < 8; ++To) dacc[To] = v4<R>{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 32; ++ks) {
+      const int kn = ks + kRing - 1;
+      if (kCross || kn < 32) {
+#pragma unroll
+        for (int u = 0; u < NH; ++u) wb[kn % kRing][u] = kn < 32 ? frag[kn * NH + u] : nfrag[(kn - 32) * NH + u];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const int T = ks >> 2, i = ks & 3;
+#pragma unroll
+      for (int To = 0; To < 8; ++To) {
+        const R wv = wb[ks % kRing][To / VW][To % VW];
+        acc[To] = mfma(wv, h[T][i], acc[To]);
+        if constexpr (kTan) dacc[To] = mfma(wv, dh[T][i], dacc[To]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the next layer's k-step p sits in slot (32 + p) mod kRing; it starts
+    // from slot p (a no-op when kRing divides 32)
+    if constexpr (kCross && 32 % kRing != 0) {
+      vh_t nx[kRing - 1][NH];
+#pragma unroll
+      for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+        for (int u = 0; u < NH; ++u) nx[p][u] = wb[(32 + p) % kRing][u];
+#pragma unroll
+      for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+        for (int u = 0; u < NH; ++u) wb[p][u] = nx[p][u];
+    }
+#pragma unroll
+    for (int To = 0; To < 8; ++To) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const R z = acc[To][q];
+        const R s = sigmoid(z, kc);
+        h[To][q] += z * s;
+        if constexpr (kTan) dh[To][q] = fma(silu_slope(z, s), dacc[To][q], dh[To][q]);
+      }
+    }
+    layer = next;
+  }
+  return layer;
+}
+
+// Encoder output layer with pairs as rows: mo[Tc] register q holds
+// m[pair drow(q, g)][16Tc + c] (dmo the same for the tangent).  Even and odd
+// k-steps accumulate separately so 4 KT independent MFMA chains are in flight;
+// the bias is added at the end so the first products do not wait for its load.
+template <int K, typename R, bool kTan = true>
+__device__ __forceinline__ void encoder_out_rows(const R* __restrict__ layer, const FloatHidden<R>& in,
+                                                 v4<R> (&mo)[K / 16], v4<R> (&dmo)[K / 16]) {
+  typedef Stream<K, R> St;
+  typedef typename St::vo_t vo_t;
+  constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
+  const int lane = phase_tid() & 63, c = lane & 15;
+  const R* __restrict__ bout = layer + K * kEncWidth;
+  v4<R> mo2[2][KT], dmo2[2][KT];
+  R b[KT];
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc) {
+    b[Tc] = bout[16 * Tc + c];
+    mo2[0][Tc] = mo2[1][Tc] = dmo2[0][Tc] = dmo2[1][Tc] = v4<R>{0, 0, 0, 0};
+  }
+  const FragStream<vo_t> frag(layer, int(K * kEncWidth * sizeof(R)));
+  vo_t wo[kRing][NO];
+#pragma unroll
+  for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+    for (int u = 0; u < NO; ++u) wo[p][u] = frag[p * NO + u];
+#pragma unroll
+  for (int ks = 0; ks < 32; ++ks) {
+    if (ks + kRing - 1 < 32) {
+#pragma unroll
+      for (int u = 0; u < NO; ++u) wo[(ks + kRing - 1) % kRing][u] = frag[(ks + kRing - 1) * NO + u];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int T = ks >> 2, i = ks & 3;
+#pragma unroll
+    for (int Tc = 0; Tc < KT; ++Tc) {
+      const R wv = wo[ks % kRing][Tc / VO][Tc % VO];
+      mo2[ks & 1][Tc] = mfma(in.h[T][i], wv, mo2[ks & 1][Tc]);
+      if constexpr (kTan) dmo2[ks & 1][Tc] = mfma(in.dh[T][i], wv, dmo2[ks & 1][Tc]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc) {
+    mo[Tc] = mo2[0][Tc] + mo2[1][Tc] + v4<R>{b[Tc], b[Tc], b[Tc], b[Tc]};
+    if constexpr (kTan) dmo[Tc] = dmo2[0][Tc] + dmo2[1][Tc];
+  }
+}
+
+// Encoder output layer with pairs as columns (the same fragments serve as the A
+// operand): register q of lane (g, c) for output tile Tc holds
+// m[pair c][16Tc + drow(q, g)].
+template <int K, typename R>
+__device__ __forceinline__ void encoder_out_cols(const R* __restrict__ layer, const FloatHidden<R>& in,
+                                                 R (&mB)[K / 16][4], R (&dmB)[K / 16][4]) {
+  typedef Stream<K, R> St;
+  typedef typename St::vo_t vo_t;
+  constexpr int KT = St::KT, NO = St::NO, VO = St::VO, kRing = St::kRingO;
+  const int lane = phase_tid() & 63, g = lane >> 4;
+  const R* __restrict__ bout = layer + K * kEncWidth;
+  v4<R> acc[KT], dacc[KT];
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc) {
+    acc[Tc] = v4<R>{bout[16 * Tc + drow<R>(0, g)], bout[16 * Tc + drow<R>(1, g)], bout[16 * Tc + drow<R>(2, g)],
+                    bout[16 * Tc + drow<R>(3, g)]};
+    dacc[Tc] = v4<R>{0, 0, 0, 0};
+  }
+  const FragStream<vo_t> frag(layer, int(K * kEncWidth * sizeof(R)));
+  vo_t wo[kRing][NO];
+#pragma unroll
+  for (int p = 0; p < kRing - 1; ++p)
+#pragma unroll
+    for (int u = 0; u < NO; ++u) wo[p][u] = frag[p * NO + u];
+#pragma unroll
+  for (int ks = 0; ks < 32; ++ks) {
+    if (ks + kRing - 1 < 32) {
+#pragma unroll
+      for (int u = 0; u < NO; ++u) wo[(ks + kRing - 1) % kRing][u] = frag[(ks + kRing - 1) * NO + u];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int T = ks >> 2, i = ks & 3;
+#pragma unroll
+    for (int Tc = 0; Tc < KT; ++Tc) {
+      const R wv = wo[ks % kRing][Tc / VO][Tc % VO];
+      acc[Tc] = mfma(wv, in.h[T][i], acc[Tc]);
+      dacc[Tc] = mfma(wv, in.dh[T][i], dacc[Tc]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int Tc = 0; Tc < KT; ++Tc)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      mB[Tc][q] = acc[Tc][q];
+      dmB[Tc][q] = dacc[Tc][q];
+    }
+}
+
+template <typename R>
+using HiddenOf = std::conditional_t<kDigits, Hidden<R>, FloatHidden<R>>;
+
+// Pair that takes row c of the feature product, so that its result registers
+// hold the pairs hrow(q, g) of the encoder's output.
+template <typename R>
+__device__ __forceinline__ int moment_pair(int c) {
+  return kDigits && sizeof(R) == 8 ? 4 * (c & 3) + (c >> 2) : c;
+}
 
 // Pass 1 on one chunk: encoder forward, moment accumulation and, when kWs,
 // the encoder tangent and the workspace write of (m, dm).  Nothing but the
@@ -924,7 +1207,7 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
       S.u.p1.geo[wave][c][2] = dz * ir;
       S.u.p1.geo[wave][c][3] = atom < 0 ? R(0) : fc;
     }
-    Hidden<R> hid;
+    HiddenOf<R> hid;
     const R* __restrict__ layer =
         encoder_hidden<K, TM, R, NW, DR, NM, kWs>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
     *next_ch = grab_chunk(&S.next_chunk[0]);
@@ -949,11 +1232,11 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
   int aa[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int p = hrow(q, g);
+    const int p = hrow<R>(q, g);
     aa[q] = p < count ? S.pair_a[start + p] : -1;
   }
   {
-    const R* geo = S.u.p1.geo[wave][moment_pair(c, R(0))];
+    const R* geo = S.u.p1.geo[wave][moment_pair<R>(c)];
     const R ax = geo[0], ay = geo[1], az = geo[2], fa = geo[3];
     R mono[NM];
     monomials_n<NM, false>(ax, ay, az, mono, mono, mono, mono);
@@ -994,13 +1277,13 @@ __device__ void pass1_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
 
   if (kWs) {
     // workspace in the B-operand order pass 2 loads, contiguous per lane:
-    // lane 16 g' + c' holds m[pair c'][16Tc + 4g' + i] at 4 KT lane' +
+    // lane 16 g' + c' holds m[pair c'][16Tc + hrow(i, g')] at 4 KT lane' +
     // 4 Tc + i (then the same for dm)
 #pragma unroll
     for (int Tc = 0; Tc < KT; ++Tc)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int off = (16 * (c >> 2) + hrow(q, g)) * (4 * KT) + Tc * 4 + (c & 3);
+        const int off = (16 * hgroup<R>(c) + hrow<R>(q, g)) * (4 * KT) + Tc * 4 + hreg<R>(c);
         wsc[off] = mo[Tc][q];
         wsc[K * 16 + off] = dmo[Tc][q];
       }
@@ -1050,7 +1333,7 @@ __device__ __forceinline__ void pass2_recompute(const FusedArgs& A, const Smem<K
   pair_delta(A, S, ch, pp, &dxd, &dyd, &dzd, &atom);
   const R dx = R(dxd), dy = R(dyd), dz = R(dzd);
   const R r = vsqrt(dx * dx + dy * dy + dz * dz);
-  Hidden<R> hid;
+  HiddenOf<R> hid;
   const R* __restrict__ layer = encoder_hidden<K, TM, R, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
   encoder_out_cols<K, R>(layer, hid, in.mB, in.dmB);
   in.pp = pp;
@@ -1125,7 +1408,7 @@ __device__ void pass2_chunk(const FusedArgs& A, Smem<K, TM, R, NW, DR, NM>& S, i
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           constexpr int DRS = moment_rows(DR, NM);
-          const R w = 16 * ta + 16 <= DRS || 16 * ta + c < DRS ? S.P[a][16 * ta + c][16 * Tc + hrow(i, g)] : R(0);
+          const R w = 16 * ta + 16 <= DRS || 16 * ta + c < DRS ? S.P[a][16 * ta + c][16 * Tc + hrow<R>(i, g)] : R(0);
           t1 = mfma(w, in.mB[Tc][i], t1);
           t2 = mfma(w, in.dmB[Tc][i], t2);
         }
@@ -1225,7 +1508,7 @@ __device__ void radial_chunk(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM
   R fc, dfc;
   cutoff(r, R(A.pi_rc), &fc, &dfc);
   if (!valid) fc = dfc = R(0);
-  Hidden<R> hid;
+  HiddenOf<R> hid;
   const R* __restrict__ layer = encoder_hidden<K, TM, R, NW, DR, NM>(A, S, S.ch_s[ch], r, chunk_table(A, S, ch), hid);
   R mB[KT][4], dmB[KT][4];
   encoder_out_cols<K, R>(layer, hid, mB, dmB);
@@ -1236,7 +1519,7 @@ __device__ void radial_chunk(const FusedArgs& A, const Smem<K, TM, R, NW, DR, NM
     for (int Tc = 0; Tc < KT; ++Tc)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int col = 16 * Tc + hrow(q, g);
+        const int col = 16 * Tc + hrow<R>(q, g);
         gr[col] = fc * mB[Tc][q];
         gp[col] = dfc * mB[Tc][q] + fc * dmB[Tc][q];
       }
@@ -1546,7 +1829,7 @@ enum Mode { kCached = 0, kRecompute = 1, kEncode = 2, kRegress = 3, kDerive = 4,
 static_assert(kCachedTileFj == kModeCachedTileFj, "mode number of the tile-reduced scatter");
 static_assert(kRegress == kModeRegress && kRadial == kModeRadial, "mode numbers of the unfused configuration");
 
-template <int K, int TM, typename R, int NW, int DR, int NM, int MODE>
+template <int K, int TM, typename R, int NW, int DR, int NM, int MODE, bool kDig>
 __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
   static_assert(TM <= 64, "the bucket table gives one lane to each atom of a tile");
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1890,12 +2173,12 @@ hipError_t launch_k(const FusedArgs& a, int n_blocks, hipStream_t s) {
   const size_t smem = sizeof(Smem<K, TM, R, NW, DR, NM>);
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused<K, TM, R, NW, DR, NM, MODE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused<K, TM, R, NW, DR, NM, MODE, kDigits>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(smem));
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_fused<K, TM, R, NW, DR, NM, MODE><<<dim3(unsigned(n_blocks)), dim3(64 * NW), smem, s>>>(a);
+  k_fused<K, TM, R, NW, DR, NM, MODE, kDigits><<<dim3(unsigned(n_blocks)), dim3(64 * NW), smem, s>>>(a);
   return hipGetLastError();
 }
 
@@ -1906,18 +2189,27 @@ hipError_t launch_mode(int mode, const FusedArgs& a, int n_blocks, hipStream_t s
     case kCached: return launch_k<K, TM, R, NW, DR, NM, kCached>(a, n_blocks, s);
     case kRecompute: return launch_k<K, TM, R, NW, DR, NM, kRecompute>(a, n_blocks, s);
     case kEncode: return launch_k<K, TM, R, NW, DR, NM, kEncode>(a, n_blocks, s);
-    case kRegress: return launch_k<K, TM, R, NW, DR, NM, kRegress>(a, n_blocks, s);
     case kDerive: return launch_k<K, TM, R, NW, DR, NM, kDerive>(a, n_blocks, s);
     case kRadial: return launch_k<K, TM, R, NW, DR, NM, kRadial>(a, n_blocks, s);
     case kCachedTileFj: return launch_k<K, TM, R, NW, DR, NM, kCachedTileFj>(a, n_blocks, s);
-    default: return hipErrorInvalidValue;
+    default: break;
   }
+  // the regression kernel has no encoder: one instantiation serves both
+  if constexpr (kDigits)
+    if (mode == kRegress) return launch_k<K, TM, R, NW, DR, NM, kRegress>(a, n_blocks, s);
+  return hipErrorInvalidValue;
 }
 #endif
 
 }  // namespace
 
-#if MLIP_FUSED_PART == 1
+#if MLIP_FUSED_DIGITS
+#define MLIP_ENTRY(name) name##_digits
+#else
+#define MLIP_ENTRY(name) name##_float
+#endif
+
+#if MLIP_FUSED_PART == 1 && MLIP_FUSED_DIGITS
 // Angular configurations: 0 = irreducible basis with l_max <= 3 (16 rows,
 // 20 monomials), 1 = Cartesian basis with l_max <= 3 (20 rows in two 16-row
 // tiles), 2 = irreducible basis with l_max 4 or 5 (up to 36 rows in three
@@ -1948,12 +2240,20 @@ int fused_tile_max(int k, int precision, int acfg) {
   return k == 64 ? 16 : 32;
 }
 
-hipError_t launch_fused(int k, int precision, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
+hipError_t launch_fused(int k, int precision, int acfg, int mode, bool digits, const FusedArgs& a, int n_blocks,
+                        hipStream_t s) {
   if (mode != kCached && (k != 32 || acfg != 0)) return hipErrorInvalidValue;
   if (acfg == 1 && k != 32) return hipErrorInvalidValue;
-  if (precision == 32) return launch_fused_f32(k, acfg, mode, a, n_blocks, s);
-  if (precision != 64) return hipErrorInvalidValue;
-  if (acfg == 2) return launch_fused_f64_high(k, a, n_blocks, s);
+  if (precision != 64 && precision != 32) return hipErrorInvalidValue;
+  digits = digits || mode == kRegress;
+  if (precision == 32) return (digits ? launch_fused_f32_digits : launch_fused_f32_float)(k, acfg, mode, a, n_blocks, s);
+  if (acfg == 2) return (digits ? launch_fused_f64_high_digits : launch_fused_f64_high_float)(k, a, n_blocks, s);
+  return (digits ? launch_fused_f64_digits : launch_fused_f64_float)(k, acfg, mode, a, n_blocks, s);
+}
+#endif
+
+#if MLIP_FUSED_PART == 1
+hipError_t MLIP_ENTRY(launch_fused_f64)(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
   if (acfg == 1) return launch_k<32, 16, double, 4, 32, 20, kCached>(a, n_blocks, s);
   switch (k) {
     case 16: return launch_k<16, 16, double, 4, 16, 20, kCached>(a, n_blocks, s);
@@ -1963,7 +2263,7 @@ hipError_t launch_fused(int k, int precision, int acfg, int mode, const FusedArg
   }
 }
 #elif MLIP_FUSED_PART == 2
-hipError_t launch_fused_f64_high(int k, const FusedArgs& a, int n_blocks, hipStream_t s) {
+hipError_t MLIP_ENTRY(launch_fused_f64_high)(int k, const FusedArgs& a, int n_blocks, hipStream_t s) {
   switch (k) {
     case 16: return launch_k<16, 16, double, 4, 48, 56, kCached>(a, n_blocks, s);
     case 32: return launch_k<32, 9, double, 4, 48, 56, kCached>(a, n_blocks, s);
@@ -1972,7 +2272,7 @@ hipError_t launch_fused_f64_high(int k, const FusedArgs& a, int n_blocks, hipStr
   }
 }
 #elif MLIP_FUSED_PART == 3
-hipError_t launch_fused_f32(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
+hipError_t MLIP_ENTRY(launch_fused_f32)(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s) {
   if (acfg == 1) return launch_k<32, 32, float, 8, 32, 20, kCached>(a, n_blocks, s);
   if (acfg == 2) {
     switch (k) {

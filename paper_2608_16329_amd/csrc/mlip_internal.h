@@ -35,10 +35,10 @@ constexpr size_t kStaticScratchHeader = 256;
 // Base-256 digits (bytes) of an encoder weight on the device (fused.hip).
 constexpr int weight_digits(int precision) { return precision == 64 ? 7 : 4; }
 // Number of values in one packed encoder table (device layout): each weight
-// matrix as digits, with a scale per row beside the bias.
-inline size_t enc_table_elems(int k, int enc_hidden, int precision) {
-  const size_t row = size_t(kEncWidth) * weight_digits(precision) / (precision / 8);
-  return 2 * kEncWidth + size_t(enc_hidden - 1) * kEncWidth * (row + 2) + size_t(k) * (row + 2);
+// matrix as digits, with a scale per row beside the bias, or as values.
+inline size_t enc_table_elems(int k, int enc_hidden, int precision, bool digits) {
+  const size_t row = digits ? size_t(kEncWidth) * weight_digits(precision) / (precision / 8) + 2 : size_t(kEncWidth) + 1;
+  return 2 * kEncWidth + (size_t(enc_hidden - 1) * kEncWidth + size_t(k)) * row;
 }
 // Number of values in one packed head table (device layout).
 inline size_t head_table_elems(int nin, int reg_hidden) {
@@ -185,6 +185,7 @@ struct mlip_ctx {
   size_t elem_bytes = 8;
   unsigned char* d_enc = nullptr;
   size_t enc_stride = 0;      // values per encoder table
+  bool digits = false;        // the encoder's products on 8-bit integer digits, else floating-point
   int n_enc = 0;
   unsigned char* d_head = nullptr;
   size_t head_stride = 0;     // values per head table
@@ -255,8 +256,11 @@ bool build_angular_table(int lmax, int angular, int rows, int cols, std::vector<
 
 // pack.hip: encoder tables (enc_table_elems values each, stride apart) from the
 // caller's blob
-hipError_t launch_pack_encoder(const double* blob, int tables, int hidden, int k, int precision, void* out, size_t stride,
-                               hipStream_t s);
+hipError_t launch_pack_encoder(const double* blob, int tables, int hidden, int k, int precision, bool digits, void* out,
+                               size_t stride, hipStream_t s);
+// raises *worst (zeroed by the caller) to the largest digit_ratio of the tables
+hipError_t launch_digit_ratio(const double* blob, int tables, int hidden, int k, double cutoff, int precision,
+                              double* worst, hipStream_t s);
 
 // neighbors.hip
 hipError_t launch_bin(const double* pos, const int32_t* types, int64_t n, const NbrGrid& g,
@@ -294,10 +298,16 @@ hipError_t launch_clear_outputs(double* forces, int64_t n, double* totals, unsig
 int angular_config(int angular, int lmax);
 void angular_table_shape(int acfg, int* rows, int* cols);
 int fused_tile_max(int k, int precision, int acfg);  // centre atoms per tile of that instantiation
-hipError_t launch_fused(int k, int precision, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
-// its parts (one object each): float64 with l_max 4..5, and float32
-hipError_t launch_fused_f64_high(int k, const FusedArgs& a, int n_blocks, hipStream_t s);
-hipError_t launch_fused_f32(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused(int k, int precision, int acfg, int mode, bool digits, const FusedArgs& a, int n_blocks,
+                        hipStream_t s);
+// its parts (one object each): float64 to l_max 3, float64 with l_max 4..5, and
+// float32, with the encoder on integer digits and on floating-point products
+hipError_t launch_fused_f64_digits(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f64_float(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f64_high_digits(int k, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f64_high_float(int k, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f32_digits(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_fused_f32_float(int k, int acfg, int mode, const FusedArgs& a, int n_blocks, hipStream_t s);
 // Modes of launch_fused used by the unfused configuration.
 constexpr int kModeRegress = 3;   // Eq. 6: G -> E_i, dE/dG
 constexpr int kModeRadial = 5;    // Eq. 2: distances -> g_rad, dg_rad/dr per entry

@@ -1,6 +1,7 @@
 // Encoder tables in the device layout (mlip_create): the first layer's values
 // as they are, each weight matrix as digits for the 16x16x64 8-bit integer MFMA
-// (fused.hip) with one scale per row, and the biases.
+// (fused.hip) with one scale per row, or as values for the 16x16x4 one, and the
+// biases; and the measure by which mlip_create chooses between the two.
 //
 // The integers of a row are round(w 2^(8 D) / scale) = sum_i d_i 256^(D - 1 - i)
 // with digits in [-128, 127], where the row's scale takes its largest weight to
@@ -20,7 +21,7 @@ constexpr int W = kEncWidth;
 
 // One work-group per row of the table's matrices (and one for the first
 // layer), one thread per column.
-template <typename R>
+template <typename R, bool kDig>
 __global__ __launch_bounds__(W) void k_pack_encoder(const double* __restrict__ blob, int hidden, int k, R* __restrict__ out,
                                                     size_t stride) {
   constexpr int D = weight_digits(8 * int(sizeof(R)));
@@ -37,8 +38,20 @@ __global__ __launch_bounds__(W) void k_pack_encoder(const double* __restrict__ b
   const int layer = row / W < hidden - 1 ? row / W : hidden - 1;
   const int o = row - layer * W, nout = layer < hidden - 1 ? W : k;
   const double* __restrict__ m = src + 2 * W + layer * square;
-  R* __restrict__ to = dst + 2 * W + size_t(layer) * W * (W * D / sizeof(R) + 2);
+  R* __restrict__ to = dst + 2 * W + size_t(layer) * W * (kDig ? W * D / sizeof(R) + 2 : W + 1);
   const double w = m[size_t(o) * W + c];
+  if constexpr (!kDig) {
+    // fragment of block (T, i) and output tile t: element [16 t + r][16 T +
+    // kin(i, g)] at lane 16 g + r, kin = 4 i + g for float64 and 4 g + i for
+    // float32 (the row map of the result registers); vw output tiles
+    // interleaved per lane, so that a 16-byte load fetches them
+    constexpr bool k64 = sizeof(R) == 8;
+    const int T = c / 16, i = k64 ? c % 16 / 4 : c % 4, g = k64 ? c % 4 : c % 16 / 4;
+    const int nt = nout / 16, vw = nt < int(16 / sizeof(R)) ? nt : int(16 / sizeof(R)), t = o / 16;
+    to[((size_t(4 * T + i) * (nt / vw) + t / vw) * 64 + 16 * g + o % 16) * vw + t % vw] = R(w);
+    if (c == 0) to[size_t(nout) * W + o] = R(m[size_t(nout) * W + o]);
+    return;
+  }
 
   // largest magnitude by bit pattern (an infinity or NaN is above all others)
   __shared__ unsigned long long part[W / 64];
@@ -75,15 +88,102 @@ __global__ __launch_bounds__(W) void k_pack_encoder(const double* __restrict__ b
   }
 }
 
+// Points in the distance at which the digits' terms are looked at.
+constexpr int kRatioPoints = 64;
+constexpr int kRatioAt = 2;  // by one work-group
+
+// The encoder of a table at distances up to the cutoff, in float64 and plain
+// order, and for each of its matrix products the largest
+//   (largest weight of the row) x (largest value of the column) / sum of the
+//   absolute terms:
+// an error of integer digits is a fixed part of the numerator, of a
+// floating-point product of the denominator (api.cpp: digits_hold).  Both the
+// values and their slopes in the distance are columns.  Infinite where a value
+// is not finite or a maximum is outside [low, high].
+__global__ __launch_bounds__(W) void k_digit_ratio(const double* __restrict__ blob, int hidden, int k, double cutoff,
+                                                   double low, double high, double* __restrict__ worst) {
+  constexpr int P = kRatioAt;
+  __shared__ double col[W][2 * P];  // values, then slopes
+  __shared__ double part[W / 64][2 * P];
+  const int o = threadIdx.x;
+  const double* __restrict__ src = blob + size_t(blockIdx.x) * (2 * W + (hidden - 1) * (size_t(W) * W + W) + size_t(k) * W + k);
+  double h[2 * P], z[2 * P];
+  auto activate = [&](int p) {
+    const double s = 1.0 / (1.0 + exp(-z[p]));
+    h[P + p] += s * (1.0 + z[p] * (1.0 - s)) * z[P + p];
+    h[p] += z[p] * s;
+  };
+  for (int p = 0; p < P; ++p) {
+    z[p] = src[o] * (cutoff * (blockIdx.y * P + p + 1) / kRatioPoints) + src[W + o];
+    z[P + p] = src[o];
+    h[p] = h[P + p] = 0.0;
+    activate(p);
+  }
+  double ratio = 0.0;
+  for (int t = 1; t <= hidden; ++t) {
+    __syncthreads();
+    for (int p = 0; p < 2 * P; ++p) {
+      col[o][p] = h[p];
+      double v = fabs(h[p]);
+      for (int x = 32; x > 0; x >>= 1) v = fmax(v, __shfl_xor(v, x, 64));
+      if ((o & 63) == 0) part[o >> 6][p] = v;
+    }
+    __syncthreads();
+    const double* __restrict__ m = src + 2 * W + (t - 1) * (size_t(W) * W + W);
+    const int nout = t < hidden ? W : k;
+    if (o < nout) {
+      double top = 0.0, sums[2 * P];
+      for (int p = 0; p < 2 * P; ++p) {
+        z[p] = p < P ? m[size_t(nout) * W + o] : 0.0;
+        sums[p] = 0.0;
+      }
+#pragma unroll 8
+      for (int c = 0; c < W; ++c) {
+        const double w = m[size_t(o) * W + c];
+        top = fmax(top, fabs(w));
+        for (int p = 0; p < 2 * P; ++p) {
+          const double x = w * col[c][p];
+          z[p] += x;
+          sums[p] += fabs(x);
+        }
+      }
+      auto fits = [&](double v) { return v == 0.0 || (v >= low && v <= high); };
+      for (int p = 0; p < 2 * P; ++p) {
+        // a NaN or infinity anywhere in the row or column is in its sum
+        const double most = fmax(part[0][p], part[1][p]);
+        const bool ok = isfinite(sums[p]) && fits(top) && fits(most);
+        const double r = top * most > 0.0 ? top * most / sums[p] : 0.0;
+        ratio = ok && r >= 0.0 ? fmax(ratio, r) : __builtin_inf();
+      }
+    }
+    if (t < hidden)
+      for (int p = 0; p < P; ++p) activate(p);
+  }
+  for (int x = 32; x > 0; x >>= 1) ratio = fmax(ratio, __shfl_xor(ratio, x, 64));
+  // non-negative doubles order like their bit patterns
+  if ((o & 63) == 0)
+    atomicMax(reinterpret_cast<unsigned long long*>(worst), static_cast<unsigned long long>(__double_as_longlong(ratio)));
+}
+
 }  // namespace
 
-hipError_t launch_pack_encoder(const double* blob, int tables, int hidden, int k, int precision, void* out, size_t stride,
-                               hipStream_t s) {
+hipError_t launch_pack_encoder(const double* blob, int tables, int hidden, int k, int precision, bool digits, void* out,
+                               size_t stride, hipStream_t s) {
   const dim3 grid(unsigned((hidden - 1) * W + k + 1), unsigned(tables));
-  if (precision == 64)
-    k_pack_encoder<double><<<grid, W, 0, s>>>(blob, hidden, k, static_cast<double*>(out), stride);
-  else
-    k_pack_encoder<float><<<grid, W, 0, s>>>(blob, hidden, k, static_cast<float*>(out), stride);
+  double* const d = static_cast<double*>(out);
+  float* const f = static_cast<float*>(out);
+  if (precision == 64 && digits) k_pack_encoder<double, true><<<grid, W, 0, s>>>(blob, hidden, k, d, stride);
+  else if (precision == 64) k_pack_encoder<double, false><<<grid, W, 0, s>>>(blob, hidden, k, d, stride);
+  else if (digits) k_pack_encoder<float, true><<<grid, W, 0, s>>>(blob, hidden, k, f, stride);
+  else k_pack_encoder<float, false><<<grid, W, 0, s>>>(blob, hidden, k, f, stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_digit_ratio(const double* blob, int tables, int hidden, int k, double cutoff, int precision,
+                              double* worst, hipStream_t s) {
+  // maxima whose scales, and their products with a value, are normal numbers
+  const double range = precision == 64 ? 0x1p+900 : 0x1p+80;
+  k_digit_ratio<<<dim3(unsigned(tables), kRatioPoints / kRatioAt), W, 0, s>>>(blob, hidden, k, cutoff, 1.0 / range, range, worst);
   return hipGetLastError();
 }
 
