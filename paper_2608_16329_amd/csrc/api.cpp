@@ -626,8 +626,10 @@ mlip_status mlip_build_neighbors(mlip_ctx* ctx, int64_t n_atoms, const double* p
   MLIP_HIP(ctx, launch_scatter(ctx->d_key, n, ctx->d_cell_start, ctx->d_cell_count, ctx->d_rowcnt, ctx->d_flags, s));
   MLIP_HIP(ctx, launch_sort_gather(pos_dev, ctx->d_key, ctx->d_cell_start, ctx->d_rowcnt, n, g, ctx->d_perm,
                                    ctx->d_spos, s));
-  MLIP_HIP(ctx, launch_rows(ctx->d_spos, ctx->d_perm, n, g, ctx->d_cell_start, ctx->d_rowcnt, nullptr, nullptr,
-                            ctx->d_flags, false, 0, 0, s));
+  // the buckets' counts, down to zero by now, become the list of cells that
+  // get a work-group where most do not
+  MLIP_HIP(ctx, launch_rows(ctx->d_spos, ctx->d_perm, ctx->d_key, n, g, ctx->d_cell_start, ctx->d_rowcnt, nullptr,
+                            nullptr, ctx->d_flags, ctx->d_cell_count, false, 0, 0, s));
   MLIP_HIP(ctx, launch_exclusive_scan_i32_to_i64(ctx->d_rowcnt, n, ctx->d_offsets, ctx->d_scan_tmp, s));
   // one copy to pinned memory brings back everything the host needs
   MLIP_HIP(ctx, launch_build_result(ctx->d_offsets + n, ctx->d_flags, ctx->d_cell_start, g, ctx->d_result, s));
@@ -655,8 +657,9 @@ mlip_status mlip_build_neighbors(mlip_ctx* ctx, int64_t n_atoms, const double* p
   // is allocated, so growing never holds both)
   if (need > ctx->cap_idx) need = need + need / 32;
   MLIP_TRY(ensure(ctx, &ctx->d_idx, &ctx->cap_idx, need, "neighbour list"));
-  MLIP_HIP(ctx, launch_rows(ctx->d_spos, ctx->d_perm, n, g, ctx->d_cell_start, ctx->d_rowcnt, ctx->d_offsets,
-                            ctx->d_idx, ctx->d_flags, true, ctx->list_tbits, ctx->list_sbits, s));
+  MLIP_HIP(ctx, launch_rows(ctx->d_spos, ctx->d_perm, ctx->d_key, n, g, ctx->d_cell_start, ctx->d_rowcnt,
+                            ctx->d_offsets, ctx->d_idx, ctx->d_flags, ctx->d_cell_count, true, ctx->list_tbits,
+                            ctx->list_sbits, s));
 
   ctx->grid = g;
   ctx->n = n;

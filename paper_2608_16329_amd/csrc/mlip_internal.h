@@ -275,10 +275,11 @@ hipError_t launch_sort_gather(const double* pos, const int32_t* key, const int32
 hipError_t launch_build_result(const int64_t* total, const int32_t* flags, const int32_t* cell_start, const NbrGrid& g,
                                BuildResult* out, hipStream_t s);
 // rows: count pass (fill false) or fill pass writing int32 indices or, with
-// tbits > 0, 16-bit codes (ListView) into idx
-hipError_t launch_rows(const double* spos, const int32_t* perm, int64_t n, const NbrGrid& g,
-                       const int32_t* cell_start, int32_t* rowcnt, const int64_t* offsets, void* idx,
-                       int32_t* flags, bool fill, int tbits, int sbits, hipStream_t s);
+// tbits > 0, 16-bit codes (ListView) into idx; cells [ncell + 1] scratch, zero
+// before the count pass and kept until the fill pass
+hipError_t launch_rows(const double* spos, const int32_t* perm, const int32_t* key, int64_t n, const NbrGrid& g,
+                       const int32_t* cell_start, int32_t* rowcnt, const int64_t* offsets, void* idx, int32_t* flags,
+                       int32_t* cells, bool fill, int tbits, int sbits, hipStream_t s);
 hipError_t launch_exclusive_scan_i32_to_i32(const int32_t* in, int64_t n, int32_t* out, int64_t* tmp,
                                             hipStream_t s);
 hipError_t launch_exclusive_scan_i32_to_i64(const int32_t* in, int64_t n, int64_t* out, int64_t* tmp,

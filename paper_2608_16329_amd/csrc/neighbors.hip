@@ -128,8 +128,28 @@ __global__ void k_sort_gather(const double* __restrict__ pos, const int32_t* __r
 constexpr int kRowThreads = 256;
 constexpr int kRowCand = 1024;   // candidates staged at a time
 constexpr int kRowAtoms = 64;    // centre atoms handled at a time
-constexpr int kRowCellsX = 1 << 22;  // work-groups along x
+constexpr int kRowCellsX = 1 << 16;  // work-groups along x
 constexpr int kMaxRuns = 27 * kMaxSpecies;
+// Systems of many cells with few atoms on average (a gas, a surface or a
+// particle in vacuum): a work-group for every cell is then mostly overhead, and
+// centres with up to kFewCand candidates in a cell of up to kFewAtoms atoms go to
+// k_rows_few instead.  A build of 1,048,576 atoms in 2.2 million cells takes
+// 792 us (11,590 with a work-group per cell, 905 with one thread per
+// centre everywhere), of 432,000 atoms in 216,000 cells 514 us (1820, 602), of
+// a slab of 1,048,576 atoms in 225,400 cells 2630 us (3195, 6035).  With fewer
+// cells, or more atoms in them, work-groups per cell are as fast or faster
+// (100,000 atoms in 54,900 cells 606 and 609 us; 1,728,000 in 216,000: 3411 and 3315; a particle of 13,500 atoms in 54,900: 609 and 4500).
+constexpr int kFewMean = 8;
+constexpr int kFewCells = 1 << 16;
+constexpr int kFewAtoms = 15;
+constexpr int kFewCand = 160;
+constexpr int kListBlocks = 16384;  // work-groups for the cells that k_rows_few leaves
+
+// Longest row into *dst, only where it raises the value: with an atomic per
+// wavefront on one address the count pass took 16.7 ms at 343,000 cells, now 8.3.
+__device__ inline void raise_longest(int32_t* dst, int longest) {
+  if (longest > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, longest);
+}
 
 // Exclusive prefix of run lengths len[0 .. n) into first[0 .. n] (n <= 2
 // kRowThreads), by all threads of the work-group.
@@ -150,24 +170,29 @@ __device__ inline void scan_runs(const int* len, int n, int* first, int* wtot) {
   __syncthreads();
 }
 
+template <bool kFill>
+struct RowShared {
+  double cx[kRowCand], cy[kRowCand], cz[kRowCand];
+  int cslot[kRowCand];              // sorted slot
+  int ccode[kFill ? kRowCand : 1];  // entry to write
+  int len[kMaxRuns], first[kMaxRuns + 1], beg[kMaxRuns], wtot[kRowThreads / 64];
+  int afirst[kMaxSpecies + 1];      // centre atoms before each species
+  int cnt[kRowAtoms];
+};
+
+// Rows of one cell's atoms (this work-group's slice of them); longest: raised to
+// the longest one of this wavefront's (count pass).
 template <bool kFill, bool kCode>
-__global__ __launch_bounds__(kRowThreads) void k_rows(const double* __restrict__ spos, const int32_t* __restrict__ perm,
-                                                      NbrGrid g, const int32_t* __restrict__ start,
-                                                      int32_t* __restrict__ rowcnt, const int64_t* __restrict__ offsets,
-                                                      void* __restrict__ idx, int32_t* __restrict__ flags, int tbits,
-                                                      int sbits) {
+__device__ __forceinline__ void rows_of_cell(RowShared<kFill>& S, int cell, const double* __restrict__ spos,
+                                             const int32_t* __restrict__ perm, const NbrGrid& g,
+                                             const int32_t* __restrict__ start, int32_t* __restrict__ rowcnt,
+                                             const int64_t* __restrict__ offsets, void* __restrict__ idx, int tbits,
+                                             int sbits, int& longest) {
   static_assert(kMaxRuns < 2 * kRowThreads, "scan_runs takes two runs per thread");
-  __shared__ double cx[kRowCand], cy[kRowCand], cz[kRowCand];
-  __shared__ int cslot[kRowCand];          // sorted slot
-  __shared__ int ccode[kFill ? kRowCand : 1];  // entry to write
-  __shared__ int len[kMaxRuns], first[kMaxRuns + 1], beg[kMaxRuns], wtot[kRowThreads / 64];
-  __shared__ int afirst[kMaxSpecies + 1];  // centre atoms before each species
-  __shared__ int cnt[kRowAtoms];
+  double *const cx = S.cx, *const cy = S.cy, *const cz = S.cz;
+  int *const cslot = S.cslot, *const ccode = S.ccode, *const len = S.len, *const first = S.first, *const beg = S.beg,
+             *const afirst = S.afirst, *const cnt = S.cnt;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // cells along x, layer by layer along z
-  const int64_t block = int64_t(blockIdx.z) * gridDim.x + blockIdx.x;
-  if (block >= g.ncell) return;
-  const int cell = int(block);
   const int cc[3] = {cell % g.nc[0], cell / g.nc[0] % g.nc[1], cell / (g.nc[0] * g.nc[1])};
   int xs[3], ys[3], zs[3];
   const int nx = adjacent(cc[0], g.nc[0], xs), ny = adjacent(cc[1], g.nc[1], ys), nz = adjacent(cc[2], g.nc[2], zs);
@@ -196,9 +221,8 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(const double* __restrict__
   // this work-group's slice of the cell's atoms
   const int a0 = int(int64_t(atoms) * blockIdx.y / gridDim.y), a1 = int(int64_t(atoms) * (blockIdx.y + 1) / gridDim.y);
   if (a0 == a1) return;
-  scan_runs(len, runs, first, wtot);
+  scan_runs(len, runs, first, S.wtot);
   const int total = first[runs];
-  int longest = 0;
   for (int g0 = a0; g0 < a1; g0 += kRowAtoms) {
     const int na = a1 - g0 < kRowAtoms ? a1 - g0 : kRowAtoms;
     __syncthreads();
@@ -268,10 +292,96 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(const double* __restrict__
       }
     }
   }
-  // only where it raises the value: with an atomic per wavefront on one address
-  // the count pass took 16.7 ms at 343,000 cells, now 8.3
-  if (!kFill && lane == 0 && longest > __hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMax(&flags[1], longest);
+}
+
+// kList: the listed cells in turn (number, then cells), else one work-group for
+// every cell, along x and layer by layer along z.
+template <bool kFill, bool kCode, bool kList>
+__global__ __launch_bounds__(kRowThreads) void k_rows(const double* __restrict__ spos, const int32_t* __restrict__ perm,
+                                                      NbrGrid g, const int32_t* __restrict__ start,
+                                                      int32_t* __restrict__ rowcnt, const int64_t* __restrict__ offsets,
+                                                      void* __restrict__ idx, int32_t* __restrict__ flags, int tbits,
+                                                      int sbits, const int32_t* __restrict__ cells) {
+  __shared__ RowShared<kFill> S;
+  int longest = 0;
+  if constexpr (kList) {
+    const int count = cells[0];
+    for (int at = blockIdx.x; at < count; at += gridDim.x) {
+      rows_of_cell<kFill, kCode>(S, cells[1 + at], spos, perm, g, start, rowcnt, offsets, idx, tbits, sbits, longest);
+      __syncthreads();
+    }
+  } else {
+    const int64_t cell = int64_t(blockIdx.z) * gridDim.x + blockIdx.x;
+    if (cell >= g.ncell) return;
+    rows_of_cell<kFill, kCode>(S, int(cell), spos, perm, g, start, rowcnt, offsets, idx, tbits, sbits, longest);
+  }
+  if (!kFill && (threadIdx.x & 63) == 0) raise_longest(&flags[1], longest);
+}
+
+// The same rows by one thread per centre, for centres with few candidates
+// (above).  The count pass lists the cells of the others in cells (number, then
+// cell indices in any order; zero on entry) for k_rows.
+template <bool kFill, bool kCode>
+__global__ void k_rows_few(const double* __restrict__ spos, const int32_t* __restrict__ perm,
+                           const int32_t* __restrict__ keys, int64_t n, NbrGrid g, const int32_t* __restrict__ start,
+                           int32_t* __restrict__ rowcnt, const int64_t* __restrict__ offsets, void* __restrict__ idx,
+                           int32_t* __restrict__ flags, int tbits, int sbits, int32_t* __restrict__ cells) {
+  const int64_t a = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  int cnt = 0;
+  if (a < n) {
+    const int key = keys[perm[a]], own = key / g.ncell, cell = key % g.ncell;
+    int xs[3], ys[3], zs[3];
+    const int nx = adjacent(cell % g.nc[0], g.nc[0], xs), ny = adjacent(cell / g.nc[0] % g.nc[1], g.nc[1], ys),
+              nz = adjacent(cell / (g.nc[0] * g.nc[1]), g.nc[2], zs);
+    // atoms of the cell, whether this is its first one, and candidates
+    int atoms = 0, cand = 0, before = 0;
+    for (int s = 0; s < g.C; ++s) {
+      const int m = start[s * g.ncell + cell + 1] - start[s * g.ncell + cell];
+      atoms += m;
+      before += s < own ? m : 0;
+    }
+    if (atoms <= kFewAtoms)
+      for (int s = 0; s < g.C; ++s)
+        for (int iz = 0; iz < nz; ++iz)
+          for (int iy = 0; iy < ny; ++iy)
+            for (int ix = 0; ix < nx; ++ix) {
+              const int k = s * g.ncell + (zs[iz] * g.nc[1] + ys[iy]) * g.nc[0] + xs[ix];
+              cand += start[k + 1] - start[k];
+            }
+    if (atoms > kFewAtoms || cand > kFewCand) {
+      if (!kFill && before == 0 && a == start[key]) cells[1 + atomicAdd(&cells[0], 1)] = cell;
+    } else {
+      const double wx = spos[3 * a], wy = spos[3 * a + 1], wz = spos[3 * a + 2];
+      const int64_t base = kFill ? offsets[a] : 0;
+      for (int s = 0; s < g.C; ++s)
+        for (int iz = 0; iz < nz; ++iz)
+          for (int iy = 0; iy < ny; ++iy)
+            for (int ix = 0; ix < nx; ++ix) {
+              const int k = s * g.ncell + (zs[iz] * g.nc[1] + ys[iy]) * g.nc[0] + xs[ix];
+              const int b0 = start[k], e = start[k + 1];
+              for (int b = b0; b < e; ++b) {
+                const double dx = fold_half(spos[3 * int64_t(b)] - wx, g.box[0], g.half[0]);
+                const double dy = fold_half(spos[3 * int64_t(b) + 1] - wy, g.box[1], g.half[1]);
+                const double dz = fold_half(spos[3 * int64_t(b) + 2] - wz, g.box[2], g.half[2]);
+                if (sqdist(dx, dy, dz) < g.rl2 && b != a) {
+                  if constexpr (kFill) {
+                    if constexpr (kCode)
+                      static_cast<uint16_t*>(idx)[base + cnt] =
+                          uint16_t((((iz * 3 + iy) * 3 + ix) << (sbits + tbits)) | (s << tbits) | (b - b0));
+                    else
+                      static_cast<int32_t*>(idx)[base + cnt] = perm[b];
+                  }
+                  ++cnt;
+                }
+              }
+            }
+      if (!kFill) rowcnt[a] = cnt;
+    }
+  }
+  if constexpr (!kFill) {
+    for (int o = 32; o > 0; o >>= 1) cnt = max(cnt, __shfl_xor(cnt, o, 64));
+    if ((threadIdx.x & 63) == 0) raise_longest(&flags[1], cnt);
+  }
 }
 
 // ---- exclusive scan: out[0..n] with out[n] = total -------------------------
@@ -449,9 +559,9 @@ hipError_t launch_build_result(const int64_t* total, const int32_t* flags, const
   return hipGetLastError();
 }
 
-hipError_t launch_rows(const double* spos, const int32_t* perm, int64_t n, const NbrGrid& g,
-                       const int32_t* cell_start, int32_t* rowcnt, const int64_t* offsets, void* idx,
-                       int32_t* flags, bool fill, int tbits, int sbits, hipStream_t s) {
+hipError_t launch_rows(const double* spos, const int32_t* perm, const int32_t* key, int64_t n, const NbrGrid& g,
+                       const int32_t* cell_start, int32_t* rowcnt, const int64_t* offsets, void* idx, int32_t* flags,
+                       int32_t* cells, bool fill, int tbits, int sbits, hipStream_t s) {
   // few cells: several work-groups share a cell's atoms, at least four each,
   // until there are about two per compute unit
   const int64_t per_cell = (n + g.ncell - 1) / g.ncell;
@@ -460,13 +570,21 @@ hipError_t launch_rows(const double* spos, const int32_t* perm, int64_t n, const
   // of 256 for every cell pass from 16.8 million cells (about 290 million BCC
   // atoms); cells past kRowCellsX go to the next layer
   const unsigned across = unsigned(std::min<int64_t>(g.ncell, kRowCellsX));
+  const bool few = g.ncell > kFewCells && n < kFewMean * int64_t(g.ncell);
   const dim3 grid(across, unsigned(std::min<int64_t>(split, 65535)), unsigned((int64_t(g.ncell) + across - 1) / across));
-  if (!fill)
-    k_rows<false, false><<<grid, kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets, idx, flags, 0, 0);
-  else if (tbits > 0)
-    k_rows<true, true><<<grid, kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets, idx, flags, tbits, sbits);
-  else
-    k_rows<true, false><<<grid, kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets, idx, flags, 0, 0);
+  auto launch = [&](auto by_cell, auto by_list, auto by_atom) {
+    if (!few) {
+      by_cell<<<grid, kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets, idx, flags, tbits, sbits, nullptr);
+      return;
+    }
+    by_atom<<<blocks_for(n, 256), 256, 0, s>>>(spos, perm, key, n, g, cell_start, rowcnt, offsets, idx, flags, tbits,
+                                               sbits, cells);
+    by_list<<<unsigned(std::min<int64_t>(n, kListBlocks)), kRowThreads, 0, s>>>(spos, perm, g, cell_start, rowcnt, offsets,
+                                                                                idx, flags, tbits, sbits, cells);
+  };
+  if (!fill) launch(k_rows<false, false, false>, k_rows<false, false, true>, k_rows_few<false, false>);
+  else if (tbits > 0) launch(k_rows<true, true, false>, k_rows<true, true, true>, k_rows_few<true, true>);
+  else launch(k_rows<true, false, false>, k_rows<true, false, true>, k_rows_few<true, false>);
   return hipGetLastError();
 }
 
