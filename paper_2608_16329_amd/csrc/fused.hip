@@ -549,16 +549,6 @@ __device__ __forceinline__ R digit_scale(const R (&h)[8][4], Digits<R>& d) {
   return sizeof(R) == 8 ? scale : scale * R(256);
 }
 
-// 4 x 4 byte transpose: byte q of out[i] is byte i of x[q].
-__device__ __forceinline__ void transpose4(const unsigned (&x)[4], unsigned (&out)[4]) {
-  const unsigned a = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), b = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
-  const unsigned e = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u), f = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
-  out[0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-  out[1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-  out[2] = __builtin_amdgcn_perm(f, e, 0x05040100u);
-  out[3] = __builtin_amdgcn_perm(f, e, 0x07060302u);
-}
-
 // Digits of the half hf of a lane's values (tiles 4 hf .. 4 hf + 3): the value
 // is rounded to an integer and a remainder, the remainder to 32 bits, by
 // adding 1.5 x 2^52, which leaves the integers in the low words (and the
@@ -588,12 +578,13 @@ __device__ __forceinline__ void make_digits(const double (&h)[8][4], double scal
     // 4 x 4 byte transposes
     const unsigned a = __builtin_amdgcn_perm(hw[1], hw[0], 0x05010400u), b = __builtin_amdgcn_perm(hw[3], hw[2], 0x05010400u);
     const unsigned e = __builtin_amdgcn_perm(hw[1], hw[0], 0x06020602u), f = __builtin_amdgcn_perm(hw[3], hw[2], 0x06020602u);
-    unsigned l[4];
-    transpose4(lw, l);
-    const unsigned w[7] = {__builtin_amdgcn_perm(f, e, 0x05040100u),
-                           __builtin_amdgcn_perm(b, a, 0x07060302u),
-                           __builtin_amdgcn_perm(b, a, 0x05040100u),
-                           l[3], l[2], l[1], l[0]};
+    const unsigned p = __builtin_amdgcn_perm(lw[1], lw[0], 0x07030602u), q = __builtin_amdgcn_perm(lw[3], lw[2], 0x07030602u);
+    const unsigned r = __builtin_amdgcn_perm(lw[1], lw[0], 0x05010400u), z = __builtin_amdgcn_perm(lw[3], lw[2], 0x05010400u);
+    const unsigned w[7] = {
+        __builtin_amdgcn_perm(f, e, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u),
+        __builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(q, p, 0x07060302u),
+        __builtin_amdgcn_perm(q, p, 0x05040100u), __builtin_amdgcn_perm(z, r, 0x07060302u),
+        __builtin_amdgcn_perm(z, r, 0x05040100u)};
 #pragma unroll
     for (int i = 0; i < 7; ++i) d.s[i][hf][t] = int(w[i] ^ 0x80808080u);
   }
@@ -607,10 +598,14 @@ __device__ __forceinline__ void make_digits(const double (&h)[8][4], double scal
 __device__ __forceinline__ void make_digits(const float (&h)[8][4], float scale, int hf, Digits<float>& d) {
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    unsigned x[4], w[4];
+    unsigned x[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) x[q] = unsigned(int(h[4 * hf + t][q] * scale)) + 0x80808080u;
-    transpose4(x, w);
+    // 4 x 4 byte transpose
+    const unsigned a = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), b = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
+    const unsigned e = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u), f = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
+    const unsigned w[4] = {__builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u),
+                           __builtin_amdgcn_perm(f, e, 0x05040100u), __builtin_amdgcn_perm(f, e, 0x07060302u)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) d.s[i][hf][t] = int(w[3 - i] ^ 0x80808080u);
   }
