@@ -44,12 +44,23 @@ def test_tile_sizes_match_oracle(edge, over, precision):
     assert abs(g["totals"][0] - g["E_i"].sum()) <= 1e-9 * np.abs(g["E_i"]).sum()
 
 
-def test_full_tiles_of_a_large_system():
-    """65,536 atoms give every work-group a dozen full tiles and more: as many
+@pytest.mark.parametrize("precision,workload,edge,most", [
+    (64, "bcc-unary-32", 32, 16),    # 65,536 atoms: 4,096 tiles of 16, 16 rounds
+    (32, "bcc-unary-32", 37, 32),    # 101,306 atoms: 3,166 tiles of 32, 12.4 rounds
+])
+def test_full_tiles_of_a_large_system(precision, workload, edge, most):
+    """Systems that give every work-group a dozen full tiles and more: as many
     atoms per tile as fit."""
-    for precision, most in ((64, 16), (32, 32)):
-        w = synth.make_workload("bcc-unary-32", seed=42, hp_overrides={"precision": precision})
-        g = gpu_eval(w.hp, w.weights, w.pos, w.types, w.box)
-        log(f"[tiles] 65,536 atoms float{precision}: {g['stats']['tile_atoms']} per tile")
-        g["pot"].close()
-        assert g["stats"]["tile_atoms"] == most or precision == 32
+    w = synth.make_workload(workload, seed=42, n=edge, hp_overrides={"precision": precision})
+    g = gpu_eval(w.hp, w.weights, w.pos, w.types, w.box)
+    st = g["stats"]
+    g["pot"].close()
+    log(f"[tiles] {len(w.pos)} atoms float{precision}: {st['tile_atoms']} per tile, {st['n_tiles']} tiles")
+    assert -(-len(w.pos) // most) >= 12 * st["n_blocks"]
+    assert st["tile_atoms"] == most
+    atoms = np.linspace(0, len(w.pos) - 1, 16).astype(np.int64)
+    E, F, V = oracle_sample(Model(w.hp, w.weights), w.pos, w.types, w.box, atoms)
+    for name, a, b in zip("EFV", (g["E_i"][atoms], g["F"][atoms], g["virial"][atoms]), (E, F, V)):
+        err = np.abs(a - b).max() / (1.0 if precision == 64 else np.abs(b).max())
+        log(f"[tiles] {name}: {err:.2e}")
+        assert err <= (TOL64 if precision == 64 else REL32)
