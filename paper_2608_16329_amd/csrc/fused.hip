@@ -447,32 +447,41 @@ __device__ __forceinline__ int hreg(int c) {
 // A float64 MFMA runs at the rate of float64 FMAs and holds the vector pipe
 // for its whole duration; 8-bit integer MFMAs run 64 times as fast (32 times a
 // float32 MFMA) and leave the vector pipe free.  The encoder's products are
-// therefore split error-free (Ozaki's scheme): with a scale per weight row and
-// per activation column, both operands become integers of balanced base-256
-// digits, X = sum_i d_i 256^(D-1-i), d_i in [-128, 127], and
+// therefore formed on digits (Ozaki's scheme): with a scale per weight row and
+// per activation column, both operands are rounded to integers of balanced
+// base-256 digits, X = sum_i d_i 256^(D-1-i), d_i in [-128, 127], and
 //   sum_k X_k Y_k = sum_i sum_j 256^(D+D'-2-i-j) sum_k d_i[k] e_j[k],
 // whose inner sums are exact in 32 bits (128 products of at most 2^14, at
-// most seven of them per i + j: below 2^24).
+// most seven of them per i + j: below 2^24).  Digit products of the lowest
+// weights are left out.  That and the rounding of both operands err by less
+// than 128 x 2^-53 (float32: 128 x 2^-29) of (largest weight of the row) x
+// (largest value of the column), where floating-point products err by a part of
+// the sum of the absolute terms; for weights whose terms are small beside that
+// product of maxima the other encoder below is taken.
 //
-// float64: seven digits (56 bits), the 28 digit products with i + j <= 6; what
-// is left out is below 2^-53 of the result's size.  Measured against a float64
-// reference the outputs are as close as with float64 MFMAs: 7.7e-16, 4.6e-15
-// and 4.0e-15 of E, F and w at 1,048,576 atoms, 8.1e-16, 4.6e-15 and 4.0e-15
-// before.  An encoder call of 16 pairs (two hidden layers) takes 59 thousand
-// cycles at 2.1 GHz, 28 us, instead of 91 thousand at 2.34 GHz, 39 us; the
-// kernel 198.6 ms instead of 251.0 ms at 1,048,576 atoms of six species.
+// float64: seven digits (56 bits), the 28 digit products with i + j <= 6.
+// Measured against a float64 reference the outputs are as close as with float64
+// MFMAs: 1.08e-15, 4.65e-15 and 4.63e-15 of E, F and w at 1,048,576 atoms,
+// 1.09e-15, 4.65e-15 and 4.64e-15 with them.  An encoder call of 16 pairs (two
+// hidden layers) takes 59 thousand cycles at 2.1 GHz, 28 us, instead of 91
+// thousand at 2.34 GHz, 39 us; the kernel 201.4 ms instead of 252.4 ms at
+// 1,048,576 atoms of six species.
 //
 // float32: four digits (32 bits) of both, the ten digit products with i + j
 // <= 3.  Three digits of an activation (24 bits under the column's scale, nine
-// products) are 1.3% faster (35.19 against 35.65 ms at 442,368 atoms), but
-// values below the column's largest then have fewer bits than float32 gives
-// them: with one hidden unit 100 times the others (and its weights in the next
-// layers 1/100) forces were off by 8.4e-6, 1.1e-6 with float32 MFMAs and 9.8e-7
-// with four digits.  With ordinary weights (131,072 atoms, six species) 1.39e-6,
-// 1.60e-6 with float32 MFMAs.
+// products) are 2% faster (85.63 against 87.11 ms, list and evaluation of
+// 1,048,576 atoms), but values below the column's largest then have fewer bits
+// than float32 gives them: with one hidden unit 100 times the others (and its
+// weights in the next layers 1/100) forces were off by 8.4e-6, 1.1e-6 with
+// float32 MFMAs and 9.8e-7 with four digits.  With ordinary weights (131,072
+// atoms, six species) 1.39e-6, 1.60e-6 with float32 MFMAs.
 //
-// What bounds it is vector issue: about 76 (float64) and 40 (float32) vector
-// instructions per activation and tangent beside 28 and 9 MFMAs.
+// What takes the time is issue, with one wavefront per SIMD (float64; two in
+// float32): counted over the whole kernel, 97 vector instructions and 22 MFMAs
+// per activation and tangent in float64, 44 and 8 in float32.  At 4 cycles each
+// that is half of a SIMD's cycles in both precisions (two thirds in float64 at
+// the 4.5 and 9 measured on one wavefront); the matrix pipe is busy for 40 and
+// 35% of them, and a wavefront waits for memory or LDS for 20 and 27% of its own.
 template <typename R>
 struct Split;
 template <>
@@ -703,10 +712,7 @@ __device__ __forceinline__ void tile_products(v4i (&w)[kTileFrags<R>], const Dig
   half_products<kRows, kNext>(w, x, S, 1, frag, next);
 }
 
-// Keeps a value in accumulation registers until its next use.
-__device__ __forceinline__ void park(double& x) { asm("" : "+a"(x)); }
-
-// Order of a region that holds the 28 MFMAs of half_products and vector work:
+// Order of a region that holds the MFMAs of half_products and vector work:
 // kValu vector instructions after each MFMA, and with kLoads each fragment's
 // load after its last use.  A 16x16x64 integer MFMA occupies the matrix pipe
 // for 16 cycles and issue for about 9, a vector instruction issue for 4 to 5

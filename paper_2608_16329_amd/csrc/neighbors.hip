@@ -126,8 +126,8 @@ __global__ void k_sort_gather(const double* __restrict__ pos, const int32_t* __r
 // of 387, of 4,994 atoms 115 instead of 1722, of 1,048,576 atoms 3.6 ms instead
 // of 7.0.
 constexpr int kRowThreads = 256;
-constexpr int kRowCand = 1024;   // candidates staged at a time
-constexpr int kRowAtoms = 64;    // centre atoms handled at a time
+constexpr int kRowCand = 1024;       // candidates staged at a time
+constexpr int kRowAtoms = 64;        // centre atoms handled at a time
 constexpr int kRowCellsX = 1 << 16;  // work-groups along x
 constexpr int kMaxRuns = 27 * kMaxSpecies;
 // Systems of many cells with few atoms on average (a gas, a surface or a
@@ -138,7 +138,8 @@ constexpr int kMaxRuns = 27 * kMaxSpecies;
 // centre everywhere), of 432,000 atoms in 216,000 cells 514 us (1820, 602), of
 // a slab of 1,048,576 atoms in 225,400 cells 2630 us (3195, 6035).  With fewer
 // cells, or more atoms in them, work-groups per cell are as fast or faster
-// (100,000 atoms in 54,900 cells 606 and 609 us; 1,728,000 in 216,000: 3411 and 3315; a particle of 13,500 atoms in 54,900: 609 and 4500).
+// (100,000 atoms in 54,900 cells 606 and 609 us; 1,728,000 in 216,000: 3411 and
+// 3315; a particle of 13,500 atoms in 54,900: 609 and 4500).
 constexpr int kFewMean = 8;
 constexpr int kFewCells = 1 << 16;
 constexpr int kFewAtoms = 15;
