@@ -215,7 +215,7 @@ void decode_row(const mlip_ctx* ctx, const HostList& h, int64_t i, const unsigne
   for (int64_t e = 0; e < len; ++e) out[e] = h.view.perm[code_slot(h.view, cand, codes[e])];
 }
 
-// Copy n <= 16 values to the host through pinned memory (a copy to the caller's
+// Copy n <= kTotals values to the host through pinned memory (a copy to the caller's
 // pageable memory is staged by the runtime), synchronising the stream.
 mlip_status read_back(mlip_ctx* ctx, const double* dev, int n, double* host) {
   MLIP_HIP(ctx, hipMemcpyAsync(ctx->h_back->values, dev, size_t(n) * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
@@ -226,7 +226,10 @@ mlip_status read_back(mlip_ctx* ctx, const double* dev, int n, double* host) {
 
 // Copy the totals to the host when asked (synchronising the stream).
 mlip_status finish_compute(mlip_ctx* ctx, const double* d_totals, double* totals_host) {
-  if (totals_host) MLIP_TRY(read_back(ctx, d_totals, 10, totals_host));
+  if (!totals_host) return MLIP_OK;
+  double t[kTotals];
+  MLIP_TRY(read_back(ctx, d_totals, kTotals, t));
+  for (int i = 0; i < 10; ++i) totals_host[i] = t[i] + t[kTotalsRest + i];
   return MLIP_OK;
 }
 
@@ -273,7 +276,7 @@ double tile_cost(const mlip_ctx* ctx, const TilePlan& t, const int32_t* sp, int6
 // fused-kernel workspace: the context's buffers (mlip_compute) or the fixed
 // device scratch (mlip_compute_noalloc).
 struct ComputeScratch {
-  double* totals;                 // [16]
+  double* totals;                 // [kTotals]
   unsigned long long* counters;   // [4]
   unsigned char* ws;              // ws_slot x n_blocks values
 };
@@ -519,7 +522,7 @@ mlip_status mlip_create(const mlip_hparams* hp, const double* weights_host, size
   if ((st = ensure(ctx, &ctx->d_enc, &cap, ctx->enc_stride * size_t(ctx->n_enc) * eb, "encoder")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_head, &cap2, head.size() * eb, "head")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_qc, &cap3, qc.size() * eb, "tables")) != MLIP_OK ||
-      (st = ensure(ctx, &ctx->d_totals, &cap4, size_t(16), "totals")) != MLIP_OK ||
+      (st = ensure(ctx, &ctx->d_totals, &cap4, size_t(kTotals), "totals")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_counters, &cap5, size_t(4), "counters")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_flags, &cap6, size_t(4), "flags")) != MLIP_OK ||
       (st = ensure(ctx, &ctx->d_result, &cap9, size_t(1), "build result")) != MLIP_OK ||
@@ -744,7 +747,7 @@ mlip_status mlip_compute_noalloc(mlip_ctx* ctx, const double* pos_dev, double* e
   if (e != hipSuccess)
     return fail_hip(ctx, e, "static scratch address (the context's device must be current)");
   unsigned char* b = static_cast<unsigned char*>(base);
-  const ComputeScratch sc{reinterpret_cast<double*>(b), reinterpret_cast<unsigned long long*>(b + 128),
+  const ComputeScratch sc{reinterpret_cast<double*>(b), reinterpret_cast<unsigned long long*>(b + kScratchCounters),
                           b + kStaticScratchHeader};
   MLIP_TRY(run_compute(ctx, pos_dev, energy_dev, forces_dev, virial_dev, totals_host, sc));
   // the context's own counter keeps the active-pair count for mlip_get_stats

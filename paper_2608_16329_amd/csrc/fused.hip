@@ -2160,7 +2160,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_fused(FusedArgs A) {
 #pragma unroll
         for (int k = 1; k < 10; ++k)
           if (tid == k) mine = v[k];
-        atomicAdd(&A.totals[tid], mine);
+        // a small system's one-atom tiles are many additions to one value: what
+        // each of them rounds away is summed too (mlip_internal.h: kTotals)
+        const double old = atomicAdd(&A.totals[tid], mine);
+        const double sum = old + mine, part = sum - old;
+        atomicAdd(&A.totals[kTotalsRest + tid], (old - (sum - part)) + (mine - part));
       }
       if (tid == 0 && kForces) atomicAdd(&A.counters[0], (unsigned long long)S.n_active);
     }

@@ -32,6 +32,14 @@ constexpr int kMonomials = 20;            // Cartesian monomials of degree <= 3
 constexpr size_t kStaticScratchBytes = size_t(256) << 20;
 constexpr size_t kStaticScratchHeader = 256;
 
+// Totals of an evaluation on the device: E and the nine virial sums, at
+// kTotalsRest + the same what rounding took from them (fused kernel; zero in
+// the unfused configuration's virial).  A sum is the two added up.
+constexpr int kTotals = 24;
+constexpr int kTotalsRest = 12;
+constexpr size_t kScratchCounters = kTotals * sizeof(double);  // place of the counters in the fixed scratch
+static_assert(kScratchCounters + 4 * sizeof(unsigned long long) <= kStaticScratchHeader, "totals and counters");
+
 // Base-256 digits (bytes) of an encoder weight on the device (fused.hip).
 constexpr int weight_digits(int precision) { return precision == 64 ? 7 : 4; }
 // Number of values in one packed encoder table (device layout): each weight
@@ -81,7 +89,7 @@ struct FusedArgs {
   double* energy;             // [n] or null
   double* forces;             // [n][3], zeroed before launch
   double* virial;             // [n][9] or null
-  double* totals;             // [10]: E, W (zeroed before launch)
+  double* totals;             // [kTotals]: E, W (zeroed before launch)
   unsigned long long* counters;  // [0] active pairs (zeroed before launch)
   void* ws;                   // per-block workspace
   long long ws_slot;          // values per block slot
@@ -127,7 +135,7 @@ struct UnfusedArgs {
   void* V;                    // [entries][16] dE_i/dg_ang
   double* forces;             // [n][3], zeroed before launch
   double* virial;             // [n][9] or null
-  double* totals;             // [10] (entries 1..9 accumulated here)
+  double* totals;             // [kTotals] (entries 1..9 accumulated here)
   double box[3];
   double inv_box[3];
   double rc2;
@@ -158,7 +166,7 @@ struct BuildResult {
 // Pinned host memory of a context for what its calls read back.
 struct HostBack {
   BuildResult build;
-  double values[16];                     // totals of an evaluation, or one reduced value
+  double values[kTotals];                // totals of an evaluation, or one reduced value
 };
 
 // Tiles of the fused kernel: centre atoms per tile, tiles, resident
@@ -225,7 +233,7 @@ struct mlip_ctx {
   unsigned char* d_ws = nullptr;  // workspace, cap_ws bytes
   size_t cap_ws = 0;
   size_t ws_slot = 0;             // values per work-group slot
-  double* d_totals = nullptr;               // [16]
+  double* d_totals = nullptr;               // [kTotals]
   unsigned long long* d_counters = nullptr; // [4]
   int32_t* d_flags = nullptr;               // [4]
   mlip::BuildResult* d_result = nullptr;    // [1]
@@ -287,7 +295,7 @@ hipError_t launch_exclusive_scan_i32_to_i64(const int32_t* in, int64_t n, int64_
 size_t scan_tmp_elems(int64_t n);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s);
-// forces [n][3], totals [16] and counters [4] of an evaluation, one launch
+// forces [n][3], totals [kTotals] and counters [4] of an evaluation, one launch
 hipError_t launch_clear_outputs(double* forces, int64_t n, double* totals, unsigned long long* counters, hipStream_t s);
 
 // fused.hip.  k 16, 32 or 64; precision 64 or 32; angular configuration

@@ -471,7 +471,7 @@ __global__ void k_clear_outputs(double* __restrict__ forces, int64_t n3, double*
                                 unsigned long long* __restrict__ counters) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n3) forces[i] = 0.0;
-  if (blockIdx.x == 0 && threadIdx.x < 16) totals[threadIdx.x] = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x < kTotals) totals[threadIdx.x] = 0.0;
   if (blockIdx.x == 0 && threadIdx.x < 4) counters[threadIdx.x] = 0;
 }
 

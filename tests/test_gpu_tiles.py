@@ -1,6 +1,8 @@
 """Atoms per tile of the fused kernel: systems that get fewer than the largest
 number (fewer tiles than work-groups, or a last round that would be nearly
 empty), up to the first that gets full tiles, against the oracle."""
+import math
+
 import numpy as np
 import pytest
 
@@ -42,6 +44,25 @@ def test_tile_sizes_match_oracle(edge, over, precision):
         log(f"[tiles] {name}: {err:.2e}")
         assert err <= (TOL64 if precision == 64 else REL32)
     assert abs(g["totals"][0] - g["E_i"].sum()) <= 1e-9 * np.abs(g["E_i"]).sum()
+
+
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("workload,edge", [("bcc-unary-32", 6), ("fcc-binary-4", 4), ("fcc-hea6-128", 9)])
+def test_totals_of_many_tiles(workload, edge, precision):
+    """The totals are the sums of the per-atom outputs to rounding, whatever the
+    number of tiles.  A tile's own sum is six additions deep (a wavefront) at
+    most, none where tiles hold one atom, and the result is rounded once; sums
+    of hundreds of tiles one after the other were 5 to 15 units of 2^-53 off."""
+    w = synth.make_workload(workload, seed=43, n=edge, hp_overrides={"precision": precision})
+    g = gpu_eval(w.hp, w.weights, w.pos, w.types, w.box)
+    tile = g["stats"]["tile_atoms"]
+    g["pot"].close()
+    out = np.column_stack([g["E_i"], g["virial"]])
+    for k in range(10):
+        exact, size = math.fsum(out[:, k]), float(np.abs(out[:, k]).sum())
+        err = abs(g["totals"][k] - exact) / size * 2.0**53
+        log(f"[tiles] {workload} {edge} float{precision}, {tile} atoms per tile: total {k} off by {err:.2f}")
+        assert err <= (2.0 if tile == 1 else 8.0)
 
 
 @pytest.mark.parametrize("precision,workload,edge,most", [
